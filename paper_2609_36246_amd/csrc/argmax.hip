@@ -39,29 +39,38 @@ __device__ __forceinline__ void queue_row(const ScoreArgs &a, const int32_t *__r
             (float)d * 0x1p-23f * (sqrtf(hh) * (1.0f + 0x1p-10f)) *
             (a.wmax_dev ? a.wmax_dev[m] : (m ? a.wmax_t : a.wmax_s));
         const float thr = theta - delta;
-        // lane s < ns: split s's maximum, second value and argmax for this row
-        const int fb = m ? F_BEST_T : F_BEST_S;
-        float best = kNegInf, sec = kNegInf;
-        int idx = 0;
-        if (lane < ns) {
-            best = a.part[((fb + 0) * MAX_SPLITS + lane) * a.pstride + j];
-            sec = a.part[((fb + 1) * MAX_SPLITS + lane) * a.pstride + j];
-            idx = __float_as_int(a.part[((fb + 2) * MAX_SPLITS + lane) * a.pstride + j]);
-        }
-        const bool scan = sec >= thr;
-        const bool one = best >= thr && !scan;
-        const uint64_t one_mask = __ballot(one);
-        const uint64_t scan_mask = __ballot(scan);
         int slot = lane == 0 ? atomicAdd(&q.n[m], 1) : 0;
         slot = __shfl(slot, 0);
         if (slot >= q.cap) continue;
         int32_t *cd = q.cand + ((int64_t)m * q.cap + slot) * q.ccap;
-        if (one) cd[__popcll(one_mask & ((1ull << lane) - 1ull))] = idx;
+        const int fb = m ? F_BEST_T : F_BEST_S;
+        int cnt = 0;
+        for (int s0 = 0; s0 < ns; s0 += 64) {
+            // lane l: split s0 + l's maximum, second value and argmax for this row
+            float best = kNegInf, sec = kNegInf;
+            int idx = 0;
+            if (s0 + lane < ns) {
+                const float *P = a.part + (int64_t)(s0 + lane) * a.sched->pstride + j;
+                best = P[(fb + 0) * a.fstride];
+                sec = P[(fb + 1) * a.fstride];
+                idx = __float_as_int(P[(fb + 2) * a.fstride]);
+            }
+            const bool scan = sec >= thr;
+            const bool one = best >= thr && !scan;
+            const uint64_t one_mask = __ballot(one);
+            const uint64_t scan_mask = __ballot(scan);
+            // (more candidates than the queue holds send the pair to the exhaustive scan)
+            const int pos = cnt + __popcll(one_mask & ((1ull << lane) - 1ull));
+            if (one && pos < q.ccap) cd[pos] = idx;
+            cnt += __popcll(one_mask);
+            uint32_t *sm = q.smask + m * SPLIT_WORDS + s0 / 32;
+            if (lane == 0 && (uint32_t)scan_mask) atomicOr(sm, (uint32_t)scan_mask);
+            if (lane == 0 && scan_mask >> 32) atomicOr(sm + 1, (uint32_t)(scan_mask >> 32));
+        }
         if (lane == 0) {
             q.qj[m * q.cap + slot] = j;
             q.qthr[m * q.cap + slot] = thr;
-            q.qcnt[m * q.cap + slot] = __popcll(one_mask);
-            if (scan_mask) atomicOr(&q.smask[m], (uint32_t)scan_mask);
+            q.qcnt[m * q.cap + slot] = cnt;
         }
     }
 }

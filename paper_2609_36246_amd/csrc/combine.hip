@@ -70,12 +70,13 @@ __device__ __forceinline__ float wave_absdot(const E *h, const E *w, int d, int 
     return acc;
 }
 
-__device__ __forceinline__ Stat load_stat(const float *P, int64_t ps, int fb, int s, int64_t j) {
+// The split record at P = part + s * pstride + j of the model whose fields start at fb.
+__device__ __forceinline__ Stat load_stat(const float *P, int64_t fs, int fb) {
     Stat r;
-    r.best = P[((fb + 0) * MAX_SPLITS + s) * ps + j];
-    r.sec = P[((fb + 1) * MAX_SPLITS + s) * ps + j];
-    r.idx = __float_as_int(P[((fb + 2) * MAX_SPLITS + s) * ps + j]);
-    r.z = P[((fb + 3) * MAX_SPLITS + s) * ps + j];
+    r.best = P[(fb + 0) * fs];
+    r.sec = P[(fb + 1) * fs];
+    r.idx = __float_as_int(P[(fb + 2) * fs]);
+    r.z = P[(fb + 3) * fs];
     return r;
 }
 
@@ -158,17 +159,31 @@ combine_kernel(ScoreArgs a, int same_scale, const int32_t *__restrict__ targets,
     const int ns = sched->n_splits;
     Stat ss = stat_identity(), st = stat_identity();
     float acc_a = 0.f, acc_b = 0.f, acc_zh = 0.f;
-    if (lane < ns) {
-        ss = load_stat(a.part, a.pstride, F_BEST_S, lane, j);
-        if (HAS_T) {
-            st = load_stat(a.part, a.pstride, F_BEST_T, lane, j);
-            if (kl) acc_a = a.part[(F_A * MAX_SPLITS + lane) * a.pstride + j];
-            if (kl_rev) acc_b = a.part[(F_B * MAX_SPLITS + lane) * a.pstride + j];
-            if (a.wide) acc_zh = a.part[(F_ZH * MAX_SPLITS + lane) * a.pstride + j];
-        }
-    }
     // the 256 x 256 kernel's fp16 weight sums follow the model whose weights it kept
     const bool zh_s = HAS_T && a.wide == 2, zh_t = HAS_T && a.wide == 1;
+    // lane l takes splits l, l + 64, ... in order
+    const int64_t fs = a.fstride, ps = sched->pstride;
+    for (int s = lane; s < ns; s += 64) {
+        const float *P = a.part + s * ps + j;
+        Stat s1 = load_stat(P, fs, F_BEST_S), t1 = stat_identity();
+        float a1 = 0.f, b1 = 0.f, z1 = 0.f;
+        if (HAS_T) {
+            t1 = load_stat(P, fs, F_BEST_T);
+            if (kl) a1 = P[F_A * fs];
+            if (kl_rev) b1 = P[F_B * fs];
+            if (a.wide) z1 = P[F_ZH * fs];
+        }
+        if (s < 64) {
+            ss = s1; st = t1;
+            acc_a = a1; acc_b = b1; acc_zh = z1;
+            continue;
+        }
+        Stat w = zh_s ? ss : st;   // the weight sum follows the same rescale
+        if (zh_s) stat_merge(w, acc_zh, s1, z1, a.cS);
+        if (zh_t) stat_merge(w, acc_zh, t1, z1, a.cT);
+        stat_merge(ss, acc_b, s1, b1, a.cS);
+        if (HAS_T) stat_merge(st, acc_a, t1, a1, a.cT);
+    }
     if (zh_s) wave_merge2(ss, acc_b, acc_zh, a.cS);
     else wave_merge(ss, acc_b, a.cS);
     if (HAS_T) {
@@ -234,21 +249,22 @@ combine_kernel(ScoreArgs a, int same_scale, const int32_t *__restrict__ targets,
 // sum their split partials in split order and scale by ln(2)/2; other valid rows get
 // +0.0. A scored row whose normalisers are NaN (bad target) stays NaN.
 __global__ void __launch_bounds__(256)
-jsd_combine_kernel(ScoreArgs a, int grid, float *__restrict__ jsd) {
+jsd_combine_kernel(ScoreArgs a, float *__restrict__ jsd) {
     const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const Sched *sched = a.sched;
     const int t_valid = sched->t_valid;
-    if (j >= t_valid) return;
     const int64_t n_sc = sched->n_scored;
     const int rows = (int)(n_sc < t_valid ? n_sc : t_valid);
+    const int n_p = (rows + MFMA_BT - 1) / MFMA_BT;
+    if (j >= t_valid) return;
     const int64_t g = a.rowmap[j] & 0x7fffffffu;
     if (j >= rows) {
         jsd[g] = 0.f;
         return;
     }
-    const int ns = pass_splits((rows + MFMA_BT - 1) / MFMA_BT, a.n_vtiles, grid);
+    const int ns = pass_splits(sched, rows, kOneChunk);
     float sum = 0.f;
-    for (int s = 0; s < ns; ++s) sum += a.part[(F_J * MAX_SPLITS + s) * a.pstride + j];
+    for (int s = 0; s < ns; ++s) sum += a.part[F_J * a.fstride + (int64_t)s * n_p * MFMA_BT + j];
     jsd[g] = 0.5f * kLn2 * sum;
 }
 
@@ -259,7 +275,7 @@ jsd_combine_kernel(ScoreArgs a, int grid, float *__restrict__ jsd) {
 // z_y (the rescale writes it in place of the stored weight). A target out of range sets
 // the error word and makes the row's normaliser NaN, as the forward combine does.
 __global__ void __launch_bounds__(256)
-dz_lse_kernel(ScoreArgs a, DzArgs z, int grid, float *__restrict__ lse_out,
+dz_lse_kernel(ScoreArgs a, DzArgs z, float *__restrict__ lse_out,
               int32_t *__restrict__ err) {
     const int lane = threadIdx.x & 63;
     const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -267,15 +283,16 @@ dz_lse_kernel(ScoreArgs a, DzArgs z, int grid, float *__restrict__ lse_out,
     const int t_rows = t_all < 0 ? 0 : (t_all < z.chunk ? t_all : z.chunk);
     if (t >= t_rows) return;
     const int64_t j = (int64_t)z.c0 + t;
-    const int ns = pass_splits((t_rows + WIDE_BT - 1) / WIDE_BT, a.n_vtiles, grid);
-    float m = kNegInf, zz = 0.f;
-    if (lane < ns) {
-        m = a.part[(F_BEST_S * MAX_SPLITS + lane) * a.pstride + j];
-        zz = a.part[(F_Z_S * MAX_SPLITS + lane) * a.pstride + j];
-    }
-    float M = m;
+    const int n_p = (t_rows + WIDE_BT - 1) / WIDE_BT;
+    const int ns = pass_splits(a.sched, t_rows, z.chunk);
+    const float *P = a.part + t;
+    const int64_t ps = (int64_t)n_p * WIDE_BT;
+    float M = kNegInf, zz = 0.f;
+    for (int s = lane; s < ns; s += 64) M = fmaxf(M, P[F_BEST_S * a.fstride + s * ps]);
     for (int off = 32; off > 0; off >>= 1) M = fmaxf(M, __shfl_xor(M, off));
-    zz = lane < ns ? zz * fast_exp2((m - M) * a.cS) : 0.f;
+    for (int s = lane; s < ns; s += 64)
+        zz += P[F_Z_S * a.fstride + s * ps] *
+              fast_exp2((P[F_BEST_S * a.fstride + s * ps] - M) * a.cS);
     for (int off = 32; off > 0; off >>= 1) zz += __shfl_xor(zz, off);
     const int64_t g = a.rowmap[j] & 0x7fffffffu;
     const int32_t y = z.targets[g];
@@ -335,10 +352,10 @@ dz_rescale_kernel(ScoreArgs a, DzArgs z, const float *__restrict__ lse) {
     }
 }
 
-hipError_t launch_dz_lse(const ScoreArgs &a, const DzArgs &z, int grid, float *lse_out,
+hipError_t launch_dz_lse(const ScoreArgs &a, const DzArgs &z, float *lse_out,
                          int32_t *err, hipStream_t st) {
     if (z.chunk <= 0 || !lse_out || !z.gy || !z.yrow || !a.part) return hipErrorInvalidValue;
-    dz_lse_kernel<<<(unsigned)((z.chunk + 3) / 4), 256, 0, st>>>(a, z, grid, lse_out, err);
+    dz_lse_kernel<<<(unsigned)((z.chunk + 3) / 4), 256, 0, st>>>(a, z, lse_out, err);
     return hipGetLastError();
 }
 
@@ -351,10 +368,10 @@ hipError_t launch_dz_rescale(const ScoreArgs &a, const DzArgs &z, const float *l
     return hipGetLastError();
 }
 
-hipError_t launch_jsd_combine(const ScoreArgs &a, float *jsd, int grid, int64_t max_rows,
+hipError_t launch_jsd_combine(const ScoreArgs &a, float *jsd, int64_t max_rows,
                               hipStream_t st) {
     if (max_rows <= 0) return hipSuccess;
-    jsd_combine_kernel<<<(unsigned)((max_rows + 255) / 256), 256, 0, st>>>(a, grid, jsd);
+    jsd_combine_kernel<<<(unsigned)((max_rows + 255) / 256), 256, 0, st>>>(a, jsd);
     return hipGetLastError();
 }
 

@@ -63,11 +63,10 @@ filter_kernel(ScoreArgs a, FilterQueue w) {
     const int64_t items = items1 + (int64_t)nqb[0] * n_vt;
     // With a split mask, only the vocabulary tiles of the marked splits of the scoring
     // pass (split s: its 256-row tiles [n_vtiles s / ns, n_vtiles (s + 1) / ns)).
-    uint32_t sm[2] = {0xFFFFFFFFu, 0xFFFFFFFFu};
     if (w.smask) {
-        sm[0] = w.smask[0];
-        sm[1] = w.smask[1];
-        if ((sm[0] | sm[1]) == 0u) return;
+        uint32_t any = 0u;
+        for (int i = 0; i < 2 * SPLIT_WORDS; ++i) any |= w.smask[i];
+        if (any == 0u) return;
     }
     const int ns = a.sched->n_splits;
     for (int64_t it = blockIdx.x; it < items; it += gridDim.x) {
@@ -78,7 +77,7 @@ filter_kernel(ScoreArgs a, FilterQueue w) {
         if (w.smask) {
             const int64_t t = vt >> 1;           // the scoring pass's 256-row tile
             const int split = (int)(((t + 1) * ns - 1) / a.n_vtiles);
-            if (!((sm[m] >> split) & 1u)) continue;
+            if (!((w.smask[m * SPLIT_WORDS + (split >> 5)] >> (split & 31)) & 1u)) continue;
         }
         const int d = m ? a.dt : a.ds;
         const uint16_t *W = (const uint16_t *)(m ? a.wt : a.ws);

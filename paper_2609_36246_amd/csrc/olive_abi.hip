@@ -30,7 +30,7 @@ struct olive_score_ctx {
     int32_t *seqbuf = nullptr;
     Sched *sched = nullptr;
     float *part = nullptr;
-    int64_t pstride = 0;
+    int64_t fstride = 0;                        // floats per partial field
     float *logp_tmp = nullptr;
     float *lse_buf = nullptr;                   // [P][2] normalisers for the JSD pass
     int32_t *flagged = nullptr;
@@ -230,7 +230,8 @@ olive_status run(olive_score_ctx *ctx, const olive_batch *b, const olive_spans *
     s = check_hip(launch_prep(*b, spans, region_only, V, ctx->seqbuf, ctx->sched, ctx->err, counts,
                               wide ? WIDE_BT : (mfma ? MFMA_BT : SIMPLE_BT), mfma ? 0 : 1,
                               n_vtiles, grid,
-                              fixed_splits, topk ? topk_min_splits(n_vtiles) : 1, st));
+                              fixed_splits, topk ? topk_min_splits(n_vtiles) : 1,
+                              ctx->fstride, jsd ? MFMA_BT : 0, kOneChunk, st));
     if (s) return s;
     s = check_hip(launch_rowmap(*b, spans, region_only, V, ctx->seqbuf, ctx->sched, ctx->rowmap,
                                 ctx->err,
@@ -248,7 +249,7 @@ olive_status run(olive_score_ctx *ctx, const olive_batch *b, const olive_spans *
     a.rowmap = ctx->rowmap;
     a.sched = ctx->sched;
     a.part = ctx->part;
-    a.pstride = ctx->pstride;
+    a.fstride = ctx->fstride;
     a.V = (int32_t)V;
     a.ds = d.d_student;
     a.dt = has_t ? d.d_teacher : 0;
@@ -328,7 +329,7 @@ olive_status run(olive_score_ctx *ctx, const olive_batch *b, const olive_spans *
         z.lse = lse_out;
         s = check_hip(launch_score_jsd(a, z, grid, st));
         if (s) return s;
-        s = check_hip(launch_jsd_combine(a, jsd, grid, T, st));
+        s = check_hip(launch_jsd_combine(a, jsd, T, st));
         if (s) return s;
     }
     if (ce) {
@@ -367,19 +368,6 @@ olive_status run_backward(olive_score_ctx *ctx, const olive_batch *b, const oliv
     const int64_t V = d.vocab;
     const int n_vtiles = (int)((V + 255) / 256);
     const int grid = ctx->n_cu;
-    // The row compaction and schedule, for position tiles of tile_rows: the normaliser
-    // pass runs the 256 x 256 kernel where the context keeps its panels, the gradient
-    // passes take 128-row tiles.
-    auto schedule = [&](int tile_rows) {
-        olive_status e = check_hip(launch_prep(*b, spans, true, V, ctx->seqbuf, ctx->sched,
-                                               ctx->err, go->counts, tile_rows, 0, n_vtiles,
-                                               grid, 1, 1, st));
-        if (!e)
-            e = check_hip(launch_rowmap(*b, spans, true, V, ctx->seqbuf, ctx->sched, ctx->rowmap,
-                                        ctx->err, nullptr, nullptr, nullptr, nullptr, nullptr,
-                                        nullptr, nullptr, nullptr, TopkOut{}, st));
-        return e;
-    };
     const bool wide = !reuse && ctx->wide;
     const int ch = ctx->bw_chunk;
     // The cross-entropy's logit gradient runs on the 256 x 256 kernel where the context
@@ -390,6 +378,20 @@ olive_status run_backward(olive_score_ctx *ctx, const olive_batch *b, const oliv
     // normalisers are known.
     const bool wide_dz = ctx->wide && !has_t && (ch % WIDE_BT == 0 || T <= ch);
     const bool online = wide && wide_dz;
+    // The row compaction and schedule, for position tiles of tile_rows: the normaliser
+    // pass runs the 256 x 256 kernel where the context keeps its panels, the gradient
+    // passes take 128-row tiles.
+    auto schedule = [&](int tile_rows) {
+        olive_status e = check_hip(launch_prep(*b, spans, true, V, ctx->seqbuf, ctx->sched,
+                                               ctx->err, go->counts, tile_rows, 0, n_vtiles,
+                                               grid, 1, 1, ctx->fstride,
+                                               wide_dz ? WIDE_BT : MFMA_BT, ch, st));
+        if (!e)
+            e = check_hip(launch_rowmap(*b, spans, true, V, ctx->seqbuf, ctx->sched, ctx->rowmap,
+                                        ctx->err, nullptr, nullptr, nullptr, nullptr, nullptr,
+                                        nullptr, nullptr, nullptr, TopkOut{}, st));
+        return e;
+    };
     olive_status s = schedule(wide && !online ? WIDE_BT : MFMA_BT);
     if (s) return s;
     ScoreArgs a;
@@ -400,7 +402,7 @@ olive_status run_backward(olive_score_ctx *ctx, const olive_batch *b, const oliv
     a.rowmap = ctx->rowmap;
     a.sched = ctx->sched;
     a.part = ctx->part;
-    a.pstride = ctx->pstride;
+    a.fstride = ctx->fstride;
     a.V = (int32_t)V;
     a.ds = d.d_student;
     a.dt = has_t ? d.d_teacher : 0;
@@ -487,7 +489,7 @@ olive_status run_backward(olive_score_ctx *ctx, const olive_batch *b, const oliv
             aw.prow = ctx->hp_rows;
             if (online) {
                 s = check_hip(launch_score_wide_dz_online(aw, z, grid, st));
-                if (!s) s = check_hip(launch_dz_lse(a, z, grid, ctx->bw_lse, ctx->err, st));
+                if (!s) s = check_hip(launch_dz_lse(a, z, ctx->bw_lse, ctx->err, st));
                 if (!s) s = check_hip(launch_dz_rescale(a, z, ctx->bw_lse, st));
             } else {
                 s = check_hip(launch_score_wide_dz(aw, z, grid, st));
@@ -610,8 +612,8 @@ bool static_carve(olive_score_ctx *c, char *base) {
     c->wmax_dev = (const float *)take(2 * sizeof(float));
     c->seqbuf = (int32_t *)take((size_t)seqbuf_entries(kStaticMaxSeqs) * sizeof(int32_t));
     c->rowmap = (uint32_t *)take((size_t)P * sizeof(uint32_t));
-    c->pstride = (P + 255) / 256 * 256;
-    c->part = (float *)take((size_t)NFIELDS * MAX_SPLITS * c->pstride * sizeof(float));
+    c->fstride = part_field_floats(P, c->n_cu);
+    c->part = (float *)take((size_t)NFIELDS * c->fstride * sizeof(float));
     c->logp_tmp = (float *)take((size_t)P * sizeof(float));
     c->flag_cap = (int)P;
     c->flagged = (int32_t *)take((size_t)4 * P * sizeof(int32_t));
@@ -624,7 +626,7 @@ bool static_carve(olive_score_ctx *c, char *base) {
     if (off > kStaticScratchBytes) return false;
     c->fxq = filter_queue_carve(c->fx_buf, c->flag_cap, FX_CCAP, &c->sched->n_fxq[0],
                                 &c->sched->n_fx_fb);
-    c->fxq.smask = &c->sched->fx_smask[0];
+    c->fxq.smask = &c->sched->fx_smask[0][0];
     return true;
 }
 
@@ -748,7 +750,7 @@ olive_status olive_score_init(olive_score_ctx **out, const olive_score_desc *des
         c->wt = c->has_t ? w_teacher : nullptr;
     }
     const int64_t P = d.max_positions;
-    c->pstride = (P + 255) / 256 * 256;
+    c->fstride = part_field_floats(P, c->n_cu);
     // One near-tie entry per compacted row at most: the list never drops a flagged row.
     c->flag_cap = (int)P;
     c->fx_window = (int)(P < kFixupWindowRows ? P : kFixupWindowRows);
@@ -756,8 +758,8 @@ olive_status olive_score_init(olive_score_ctx **out, const olive_score_desc *des
     if (!s) s = dev_alloc(&c->seqbuf, (size_t)seqbuf_entries(d.max_seqs) * sizeof(int32_t));
     if (!s) s = dev_alloc(&c->sched, sizeof(Sched));
     if (!s)
-        s = dev_alloc(&c->part, (size_t)(c->topk ? NFIELDS_TOPK : NFIELDS) * MAX_SPLITS *
-                                    c->pstride * sizeof(float));
+        s = dev_alloc(&c->part, (size_t)(c->topk ? NFIELDS_TOPK : NFIELDS) * c->fstride *
+                                    sizeof(float));
     if (!s && c->topk) {
         s = dev_alloc(&c->tk_buf, topk_work_bytes(P));
         if (!s) c->tkw = topk_carve(c->tk_buf, P, &c->sched->n_tkq[0], &c->sched->n_tk_fb);
@@ -767,7 +769,7 @@ olive_status olive_score_init(olive_score_ctx **out, const olive_score_desc *des
         if (!s) {
             c->fxq = filter_queue_carve(c->fx_buf, c->flag_cap, FX_CCAP, &c->sched->n_fxq[0],
                                         &c->sched->n_fx_fb);
-            c->fxq.smask = &c->sched->fx_smask[0];   // the greedy filter reads marked splits
+            c->fxq.smask = &c->sched->fx_smask[0][0];   // the greedy filter reads marked splits
         }
     }
     if (!s && c->bw) {

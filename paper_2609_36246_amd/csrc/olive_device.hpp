@@ -59,10 +59,6 @@ __device__ __forceinline__ float load_elem<uint16_t>(const uint16_t *p, int64_t 
     return bf16_bits_to_f32(p[i]);
 }
 
-// Vocabulary splits of a pass over n_p position tiles on a persistent grid of G
-// workgroups: the count minimising (rounds of the grid) x (vocabulary tiles per
-// split), the smallest among equals. The passes over the scored rows (logit gradient,
-// Jensen-Shannon) and the combine of the latter use it alike.
 // Work unit q -> (position tile p, vocabulary split s) of n_p tiles x ns splits: units
 // cycle through groups of SG splits, so that the 32 workgroups of an XCD, which take
 // consecutive units, share 32 / SG position tiles x SG splits. Two or more splits left
@@ -89,15 +85,41 @@ __device__ __forceinline__ void unit_tile_split(int64_t q, int n_p, int ns, int 
     }
 }
 
-__device__ __forceinline__ int pass_splits(int n_p, int n_vtiles, int G) {
-    const int smax = n_vtiles < MAX_SPLITS ? n_vtiles : MAX_SPLITS;
-    int ns = 1;
-    int64_t best = -1;
-    for (int sc = 1; sc <= smax; ++sc) {
-        const int64_t cost = (((int64_t)n_p * sc + G - 1) / G) * ((n_vtiles + sc - 1) / sc);
-        if (best < 0 || cost < best) { best = cost; ns = sc; }
+// Vocabulary splits of a pass over n_p position tiles of tile_rows rows on a persistent
+// grid of G workgroups: the count in [smin, smax] minimising (rounds of the grid) x
+// (vocabulary tiles per split), the smallest among equals. More than MAX_SPLITS only
+// where the units then still fit one round and the partials one field of fstride floats:
+// with few position tiles MAX_SPLITS units each leave compute units idle (160 positions
+// at V = 151936, d 2048 + 4096: 2.40 ms a call with 32 units on 256 compute units, 0.48 ms
+// with 198, the fewest that give each at most 3 vocabulary tiles).
+// Called by whole wavefronts: lane l tries the counts l + 1, l + 65, ...
+__device__ __forceinline__ int pick_splits(int n_p, int n_vtiles, int G, int smin, int smax,
+                                           int tile_rows, int64_t fstride) {
+    smax = n_vtiles < smax ? n_vtiles : smax;
+    smin = smin < smax ? smin : smax;
+    uint64_t best = ~0ull;
+    for (int s = (int)(threadIdx.x & 63) + 1; s <= smax; s += 64) {
+        if (s < smin) continue;
+        if (s > MAX_SPLITS &&
+            ((int64_t)n_p * s > G || (int64_t)n_p * tile_rows * s > fstride))
+            continue;
+        // n_p < 2^31 / 128: the units of MAX_SPLITS splits fit 32 bits
+        const uint32_t rounds = ((uint32_t)n_p * (uint32_t)s + (uint32_t)G - 1u) / (uint32_t)G;
+        const uint32_t per = (uint32_t)(n_vtiles + s - 1) / (uint32_t)s;
+        const uint64_t key = ((uint64_t)rounds * per << 9) | (uint64_t)s;
+        best = key < best ? key : best;
     }
-    return ns;
+    for (int off = 32; off > 0; off >>= 1) {
+        const uint64_t o = __shfl_xor(best, off);
+        best = o < best ? o : best;
+    }
+    return __builtin_amdgcn_readfirstlane((int)(best & 511u));
+}
+
+// The splits of a pass over the scored rows (logit gradient, Jensen-Shannon), or over t_rows
+// of them at most `chunk` at a time, as the preparation kernel chose them.
+__device__ __forceinline__ int pass_splits(const Sched *sched, int t_rows, int chunk) {
+    return sched->pass_splits[t_rows == chunk ? 0 : 1];
 }
 
 // Running max / second max / lowest argmax / rescaled exp-sum of one model, and

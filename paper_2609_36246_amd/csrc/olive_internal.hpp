@@ -10,7 +10,8 @@
 namespace olive {
 
 // Per-(row, vocabulary split) partial statistics, stored as planes of floats:
-// plane (field * max_splits + split) holds one value per compacted row.
+// field f of split s and row j lies at part[f * fstride + s * pstride + j], where pstride is
+// the pass's rows rounded up to its position tiles (chosen on the device with the splits).
 //   BEST/SEC: largest and second-largest raw logit (unscaled h.W) seen;
 //   IDX:      lowest vocabulary index attaining BEST (int32 bits);
 //   Z:        sum_v exp(s * (z_v - BEST)) over the split;
@@ -53,8 +54,8 @@ struct FilterQueue {
     int32_t *qcnt;       // [2][cap] candidates found (may exceed ccap)
     int32_t *cand;       // [2][cap][ccap] their vocabulary indices
     int32_t *fb;         // [2 cap] (model * cap + slot) of the pairs for the exhaustive scan
-    uint32_t *smask;     // device [2] or null: per model, the vocabulary splits (bit s) the
-                         // filter reads; null: every split
+    uint32_t *smask;     // device [2][SPLIT_WORDS] or null: per model, the vocabulary splits
+                         // (bit s % 32 of word s / 32) the filter reads; null: every split
     int cap, ccap;
 };
 size_t filter_queue_bytes(int64_t cap, int ccap);
@@ -71,6 +72,14 @@ struct TopkWork {
 size_t topk_work_bytes(int64_t cap);
 TopkWork topk_carve(void *base, int64_t cap, int32_t *n, int32_t *nfb);
 
+// Vocabulary splits of a pass: up to MAX_SPLITS for any number of position tiles, and up to
+// MAX_SPLITS_FEW where the position tiles are so few that MAX_SPLITS of them each would not
+// fill the persistent grid (tiles x splits <= workgroups then; pick_splits).
+constexpr int MAX_SPLITS = 32;
+constexpr int MAX_SPLITS_FEW = 256;
+constexpr int SPLIT_WORDS = MAX_SPLITS_FEW / 32;
+constexpr int kOneChunk = 0x7fffffff;   // a pass that takes the scored rows in one chunk
+
 // Device-side schedule of one call, written by the preparation kernel.
 struct Sched {
     int32_t t_valid;    // compacted rows: valid positions, or only the in-region ones when
@@ -80,13 +89,16 @@ struct Sched {
     int32_t n_units;    // n_ptiles * n_splits
     int64_t n_scored;   // in-region valid positions
     int32_t n_flagged;  // rows queued for the near-tie argmax re-decision
+    int32_t pstride;    // floats from one split's partials to the next: n_ptiles tiles of rows
+    int32_t pass_splits[2];   // vocabulary splits of a pass over the scored rows: of a full
+                              // chunk of them, and of the last, shorter one
     int32_t cu_bad;     // cu_seqlens malformed: nothing is scored
     int32_t n_tkq[2];   // (row, model) pairs whose top-K field needs the vocabulary filter
     int32_t n_tk_fb;    // pairs of those that need the exhaustive exact scan
     int32_t n_fxq[2];   // near-tie (row, model) pairs of the greedy re-decision (MFMA path)
     int32_t n_fx_fb;    // pairs of those that need the exhaustive exact scan
-    uint32_t fx_smask[2];   // per model: vocabulary splits (bit s) the re-decision's filter
-                            // must read
+    uint32_t fx_smask[2][SPLIT_WORDS];   // per model: vocabulary splits (bit s % 32 of word
+                                         // s / 32) the re-decision's filter must read
 };
 
 // Top-K outputs of a call (null pointers: not requested).
@@ -112,7 +124,6 @@ constexpr int MFMA_BT = 128;     // positions per tile (MFMA N)
 constexpr int WIDE_BT = 256;     // positions per tile of the 256 x 256 kernel
 constexpr int SIMPLE_BT = 16;    // positions per tile of the generic kernel
 constexpr int SIMPLE_VC = 256;   // vocabulary chunk of the generic kernel
-constexpr int MAX_SPLITS = 32;   // vocabulary splits a call may use
 
 struct ScoreArgs {
     const void *hs, *ht;         // hidden states [T][d] (caller)
@@ -120,7 +131,7 @@ struct ScoreArgs {
     const uint32_t *rowmap;      // [t_valid]: packed row | in-region << 31
     const Sched *sched;
     float *part;                 // partial planes
-    int64_t pstride;             // floats per plane
+    int64_t fstride;             // floats per field (part_field_floats)
     int32_t V, ds, dt;
     int32_t n_vtiles;            // vocabulary tiles (MFMA) or chunks (generic)
     float cS, cT;                // s * log2(e)
@@ -189,6 +200,15 @@ struct GemmArgs {
     int a_prows;
 };
 
+// Floats one partial field holds: MAX_SPLITS splits of every row a call may have, or
+// MAX_SPLITS_FEW splits of few position tiles (tiles x splits <= n_cu, 256 rows a tile at
+// most).
+inline int64_t part_field_floats(int64_t max_positions, int n_cu) {
+    const int64_t all = (max_positions + 255) / 256 * 256 * MAX_SPLITS;
+    const int64_t few = (int64_t)n_cu * 256;
+    return all > few ? all : few;
+}
+
 // Host-side launchers (each defined beside its kernel).
 hipError_t launch_filter(const ScoreArgs &a, const FilterQueue &q, hipStream_t st);
 hipError_t launch_repack(const void *w_dv, void *w_vd, int64_t d, int64_t V, int elem_bytes,
@@ -196,7 +216,8 @@ hipError_t launch_repack(const void *w_dv, void *w_vd, int64_t d, int64_t V, int
 hipError_t launch_prep(const olive_batch &b, const olive_spans *spans, bool region_only,
                        int64_t V, int32_t *seqbuf, Sched *sched, int32_t *err, int64_t *counts,
                        int tile_rows, int policy, int n_vtiles, int grid, int fixed_splits,
-                       int min_splits, hipStream_t st);
+                       int min_splits, int64_t fstride, int pass_tile, int pass_chunk,
+                       hipStream_t st);
 hipError_t launch_rowmap(const olive_batch &b, const olive_spans *spans, bool region_only,
                          int64_t V, const int32_t *seqbuf,
                          const Sched *sched, uint32_t *rowmap, int32_t *err, float *logp_s,
@@ -211,8 +232,8 @@ hipError_t launch_score_wide(const ScoreArgs &a, bool same_scale, bool has_t, bo
 hipError_t launch_score_wide_dz(const ScoreArgs &a, const DzArgs &z, int grid, hipStream_t st);
 hipError_t launch_score_wide_dz_online(const ScoreArgs &a, const DzArgs &z, int grid,
                                        hipStream_t st);
-hipError_t launch_dz_lse(const ScoreArgs &a, const DzArgs &z, int grid, float *lse_out,
-                         int32_t *err, hipStream_t st);
+hipError_t launch_dz_lse(const ScoreArgs &a, const DzArgs &z, float *lse_out, int32_t *err,
+                         hipStream_t st);
 hipError_t launch_dz_rescale(const ScoreArgs &a, const DzArgs &z, const float *lse,
                              hipStream_t st);
 hipError_t launch_panel_w(const void *w, int64_t V, int d, int64_t vpad, void *out,
@@ -222,7 +243,7 @@ hipError_t launch_panel_h(const void *h, int d, const uint32_t *rowmap, const Sc
 hipError_t launch_score_dz(const ScoreArgs &a, const DzArgs &z, bool has_t, int grid,
                            hipStream_t st);
 hipError_t launch_score_jsd(const ScoreArgs &a, const JsdArgs &z, int grid, hipStream_t st);
-hipError_t launch_jsd_combine(const ScoreArgs &a, float *jsd, int grid, int64_t max_rows,
+hipError_t launch_jsd_combine(const ScoreArgs &a, float *jsd, int64_t max_rows,
                               hipStream_t st);
 hipError_t launch_gemm(const GemmArgs &g, int grid, hipStream_t st);
 hipError_t launch_panel_t(const void *w, int64_t V, int d, int64_t vp, void *out,

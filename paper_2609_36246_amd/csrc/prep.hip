@@ -85,7 +85,8 @@ prep_kernel(const int32_t *__restrict__ cu, const int32_t *__restrict__ cut,
             SpanArgs sp, int32_t region_only, int32_t *__restrict__ seqbuf,
             Sched *__restrict__ sched, int32_t *__restrict__ err, int64_t *__restrict__ counts,
             int32_t tile_rows, int32_t policy, int32_t n_vtiles, int32_t grid,
-            int32_t fixed_splits, int32_t min_splits) {
+            int32_t fixed_splits, int32_t min_splits, int32_t max_splits, int64_t fstride,
+            int32_t pass_tile, int32_t pass_chunk) {
     __shared__ int s_bad, s_badoff;
     __shared__ int s_scan[PREP_THREADS];
     __shared__ int s_scan_sc[PREP_THREADS];
@@ -125,7 +126,9 @@ prep_kernel(const int32_t *__restrict__ cu, const int32_t *__restrict__ cut,
             sched->n_scored = 0; sched->n_flagged = 0; sched->cu_bad = 1;
             sched->n_tkq[0] = 0; sched->n_tkq[1] = 0; sched->n_tk_fb = 0;
             sched->n_fxq[0] = 0; sched->n_fxq[1] = 0; sched->n_fx_fb = 0;
-            sched->fx_smask[0] = 0u; sched->fx_smask[1] = 0u;
+            sched->pstride = 0;
+            sched->pass_splits[0] = 1; sched->pass_splits[1] = 1;
+            for (int w = 0; w < 2 * SPLIT_WORDS; ++w) sched->fx_smask[0][w] = 0u;
             if (counts) { counts[0] = 0; counts[1] = 0; }
         }
         return;
@@ -199,28 +202,25 @@ prep_kernel(const int32_t *__restrict__ cu, const int32_t *__restrict__ cut,
         valid += s_val[0];
         __syncthreads();
     }
+    if (tid >= 192) return;
+    if (tid >= 64) {   // the later passes over the scored rows, in tiles of pass_tile rows
+        if (pass_tile == 0) return;
+        const int full = tid < 128 ? 1 : 0;
+        const int rows = full ? pass_chunk : (int)(scored % pass_chunk);
+        const int s = pick_splits((rows + pass_tile - 1) / pass_tile, n_vtiles, grid, 1,
+                                  MAX_SPLITS_FEW, pass_tile, fstride);
+        if ((tid & 63) == 0) sched->pass_splits[1 - full] = s;
+        return;
+    }
+    const int t_valid = carry;   // compacted rows: valid, or in-region when region-only
+    const int n_p = (t_valid + tile_rows - 1) / tile_rows;
+    int ns = fixed_splits < n_vtiles ? fixed_splits : n_vtiles;
+    if (policy == 0)
+        ns = pick_splits(n_p, n_vtiles, grid, min_splits, max_splits, tile_rows, fstride);
+    if (ns < 1) ns = 1;
     if (tid == 0) {
         cvalid[B] = carry;
         cscored[B] = carry_sc;
-        int t_valid = carry;   // compacted rows: valid, or in-region when region-only
-        int n_p = (t_valid + tile_rows - 1) / tile_rows;
-        int ns = 1;
-        if (policy == 0) {
-            // Minimise (rounds of the persistent grid) x (vocabulary tiles per split).
-            long long best = -1;
-            int smax = n_vtiles < MAX_SPLITS ? n_vtiles : MAX_SPLITS;
-            const int smin = min_splits < smax ? min_splits : smax;
-            for (int s = smin; s <= smax; ++s) {
-                long long units = (long long)n_p * s;
-                long long rounds = (units + grid - 1) / grid;
-                long long per = (n_vtiles + s - 1) / s;
-                long long cost = rounds * per;
-                if (best < 0 || cost < best) { best = cost; ns = s; }
-            }
-        } else {
-            ns = fixed_splits < n_vtiles ? fixed_splits : n_vtiles;
-            if (ns < 1) ns = 1;
-        }
         sched->t_valid = t_valid;
         sched->n_ptiles = n_p;
         sched->n_splits = ns;
@@ -229,7 +229,8 @@ prep_kernel(const int32_t *__restrict__ cu, const int32_t *__restrict__ cut,
         sched->n_flagged = 0;
         sched->n_tkq[0] = 0; sched->n_tkq[1] = 0; sched->n_tk_fb = 0;
         sched->n_fxq[0] = 0; sched->n_fxq[1] = 0; sched->n_fx_fb = 0;
-        sched->fx_smask[0] = 0u; sched->fx_smask[1] = 0u;
+        sched->pstride = n_p * tile_rows;
+        for (int w = 0; w < 2 * SPLIT_WORDS; ++w) sched->fx_smask[0][w] = 0u;
         sched->cu_bad = 0;
         if (counts) { counts[0] = scored; counts[1] = valid; }
     }
@@ -407,13 +408,16 @@ static SpanArgs span_args(const olive_spans *s) {
 hipError_t launch_prep(const olive_batch &b, const olive_spans *spans, bool region_only,
                        int64_t V, int32_t *seqbuf, Sched *sched, int32_t *err, int64_t *counts,
                        int tile_rows, int policy, int n_vtiles, int grid, int fixed_splits,
-                       int min_splits, hipStream_t st) {
+                       int min_splits, int64_t fstride, int pass_tile, int pass_chunk,
+                       hipStream_t st) {
     (void)V;
     prep_kernel<<<1, PREP_THREADS, 0, st>>>(b.cu_seqlens, b.cut, b.valid_len, b.num_seqs,
                                             b.total_positions, b.region, span_args(spans),
                                             region_only ? 1 : 0, seqbuf, sched, err, counts,
                                             tile_rows, policy, n_vtiles, grid, fixed_splits,
-                                            min_splits);
+                                            min_splits,
+                                            min_splits > 1 ? MAX_SPLITS : MAX_SPLITS_FEW,
+                                            fstride, pass_tile, pass_chunk);
     return hipGetLastError();
 }
 

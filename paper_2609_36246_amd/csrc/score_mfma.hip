@@ -626,19 +626,19 @@ struct Kernel {
                     }
                     const int j = p * BT + L.wt * 64 + cb * 32 + L.l32;
                     if (j < t_valid) {
-                        float *P = a.part;
-                        const int64_t ps = a.pstride;
-                        P[(F_BEST_S * MAX_SPLITS + s) * ps + j] = RS[cb].best;
-                        P[(F_SEC_S * MAX_SPLITS + s) * ps + j] = RS[cb].sec;
-                        P[(F_IDX_S * MAX_SPLITS + s) * ps + j] = __int_as_float(RS[cb].idx);
-                        P[(F_Z_S * MAX_SPLITS + s) * ps + j] = RS[cb].z;
+                        const int64_t fs = a.fstride;
+                        float *P = a.part + (int64_t)s * a.sched->pstride + j;
+                        P[F_BEST_S * fs] = RS[cb].best;
+                        P[F_SEC_S * fs] = RS[cb].sec;
+                        P[F_IDX_S * fs] = __int_as_float(RS[cb].idx);
+                        P[F_Z_S * fs] = RS[cb].z;
                         if (HAS_T) {
-                            P[(F_BEST_T * MAX_SPLITS + s) * ps + j] = RT[cb].best;
-                            P[(F_SEC_T * MAX_SPLITS + s) * ps + j] = RT[cb].sec;
-                            P[(F_IDX_T * MAX_SPLITS + s) * ps + j] = __int_as_float(RT[cb].idx);
-                            P[(F_Z_T * MAX_SPLITS + s) * ps + j] = RT[cb].z;
-                            P[(F_A * MAX_SPLITS + s) * ps + j] = AA[cb];
-                            if (REV) P[(F_B * MAX_SPLITS + s) * ps + j] = BB[cb];
+                            P[F_BEST_T * fs] = RT[cb].best;
+                            P[F_SEC_T * fs] = RT[cb].sec;
+                            P[F_IDX_T * fs] = __int_as_float(RT[cb].idx);
+                            P[F_Z_T * fs] = RT[cb].z;
+                            P[F_A * fs] = AA[cb];
+                            if (REV) P[F_B * fs] = BB[cb];
                             if (lists) {
                                 // the other half's top-8 into this one's: the 8 dropped
                                 // raise the floor
@@ -656,12 +656,11 @@ struct Kernel {
                                     }
 #pragma unroll
                                     for (int e = 0; e < 8; ++e) {
-                                        P[((F_TK + m * TK_FIELDS + e) * MAX_SPLITS + s) * ps + j] =
-                                            Q8v[m][cb][e];
-                                        P[((F_TK + m * TK_FIELDS + 8 + e) * MAX_SPLITS + s) * ps +
-                                          j] = __int_as_float(Q8i[m][cb][e]);
+                                        P[(F_TK + m * TK_FIELDS + e) * fs] = Q8v[m][cb][e];
+                                        P[(F_TK + m * TK_FIELDS + 8 + e) * fs] =
+                                            __int_as_float(Q8i[m][cb][e]);
                                     }
-                                    P[((F_TK + m * TK_FIELDS + 16) * MAX_SPLITS + s) * ps + j] = fl;
+                                    P[(F_TK + m * TK_FIELDS + 16) * fs] = fl;
                                 }
                             }
                         }
@@ -689,7 +688,7 @@ struct Kernel {
         const int t_rows = t_all < 0 ? 0 : (t_all < z.chunk ? t_all : z.chunk);
         const int n_p = (t_rows + BT - 1) / BT;
         const int G = gridDim.x;
-        const int ns = pass_splits(n_p, a.n_vtiles, G);
+        const int ns = pass_splits(a.sched, t_rows, z.chunk);
         const int64_t n_units = (int64_t)n_p * ns;
         Lane L;
         L.lane = threadIdx.x & 63;
@@ -843,7 +842,7 @@ struct Kernel {
         const int rows = (int)(n_sc < t_valid ? n_sc : t_valid);
         const int n_p = (rows + BT - 1) / BT;
         const int G = gridDim.x;
-        const int ns = pass_splits(n_p, a.n_vtiles, G);
+        const int ns = pass_splits(a.sched, rows, kOneChunk);
         const int64_t n_units = (int64_t)n_p * ns;
         Lane L;
         L.lane = threadIdx.x & 63;
@@ -936,7 +935,7 @@ struct Kernel {
 #pragma unroll
                 for (int cb = 0; cb < 2; ++cb)
                     if (ok[cb])
-                        a.part[(F_J * MAX_SPLITS + s) * a.pstride + tcol[cb]] =
+                        a.part[F_J * a.fstride + (int64_t)s * n_p * BT + tcol[cb]] =
                             acc[cb] + xs[(L.wt * 2 + cb) * 32 + L.l32];
             }
             compiler_fence();

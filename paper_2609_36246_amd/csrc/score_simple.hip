@@ -143,19 +143,19 @@ score_simple_kernel(ScoreArgs a, int same_scale) {
         }
         const int j = p * SIMPLE_BT + wid * 4 + rr;
         if (lane == 0 && j < t_valid) {
-            float *P = a.part;
-            const int64_t ps = a.pstride;
-            P[(F_BEST_S * MAX_SPLITS + s) * ps + j] = st_s[rr].best;
-            P[(F_SEC_S * MAX_SPLITS + s) * ps + j] = st_s[rr].sec;
-            P[(F_IDX_S * MAX_SPLITS + s) * ps + j] = __int_as_float(st_s[rr].idx);
-            P[(F_Z_S * MAX_SPLITS + s) * ps + j] = st_s[rr].z;
+            const int64_t fs = a.fstride;
+            float *P = a.part + (int64_t)s * a.sched->pstride + j;
+            P[F_BEST_S * fs] = st_s[rr].best;
+            P[F_SEC_S * fs] = st_s[rr].sec;
+            P[F_IDX_S * fs] = __int_as_float(st_s[rr].idx);
+            P[F_Z_S * fs] = st_s[rr].z;
             if (HAS_T) {
-                P[(F_BEST_T * MAX_SPLITS + s) * ps + j] = st_t[rr].best;
-                P[(F_SEC_T * MAX_SPLITS + s) * ps + j] = st_t[rr].sec;
-                P[(F_IDX_T * MAX_SPLITS + s) * ps + j] = __int_as_float(st_t[rr].idx);
-                P[(F_Z_T * MAX_SPLITS + s) * ps + j] = st_t[rr].z;
-                P[(F_A * MAX_SPLITS + s) * ps + j] = acc_a[rr];
-                P[(F_B * MAX_SPLITS + s) * ps + j] = acc_b[rr];
+                P[F_BEST_T * fs] = st_t[rr].best;
+                P[F_SEC_T * fs] = st_t[rr].sec;
+                P[F_IDX_T * fs] = __int_as_float(st_t[rr].idx);
+                P[F_Z_T * fs] = st_t[rr].z;
+                P[F_A * fs] = acc_a[rr];
+                P[F_B * fs] = acc_b[rr];
             }
         }
     }

@@ -464,21 +464,21 @@ struct Wide {
                 const Run &RS = M2 == 0 ? R2 : R1, &RT = M2 == 0 ? R1 : R2;
                 const int j = p * XT + L.wid * 64 + cb * 16 + L.l16;
                 if (L.g == 0 && j < t_valid) {
-                    float *P = a.part;
-                    const int64_t ps = a.pstride;
+                    const int64_t fs = a.fstride;
+                    float *P = a.part + (int64_t)s * a.sched->pstride + j;
                     // the first model's exp-sum carries the weights' 2^15 (exact)
                     const float zs1 = HAS_T ? 0x1p-15f : 1.f;
-                    P[(F_BEST_S * MAX_SPLITS + s) * ps + j] = RS.best;
-                    P[(F_SEC_S * MAX_SPLITS + s) * ps + j] = RS.sec;
-                    P[(F_IDX_S * MAX_SPLITS + s) * ps + j] = __int_as_float(RS.idx);
-                    P[(F_Z_S * MAX_SPLITS + s) * ps + j] = M1 ? RS.z : RS.z * zs1;
+                    P[F_BEST_S * fs] = RS.best;
+                    P[F_SEC_S * fs] = RS.sec;
+                    P[F_IDX_S * fs] = __int_as_float(RS.idx);
+                    P[F_Z_S * fs] = M1 ? RS.z : RS.z * zs1;
                     if (!HAS_T) continue;
-                    P[(F_BEST_T * MAX_SPLITS + s) * ps + j] = RT.best;
-                    P[(F_SEC_T * MAX_SPLITS + s) * ps + j] = RT.sec;
-                    P[(F_IDX_T * MAX_SPLITS + s) * ps + j] = __int_as_float(RT.idx);
-                    P[(F_Z_T * MAX_SPLITS + s) * ps + j] = M1 ? RT.z * zs1 : RT.z;
-                    P[((REV ? F_B : F_A) * MAX_SPLITS + s) * ps + j] = aa;
-                    P[(F_ZH * MAX_SPLITS + s) * ps + j] = zh;
+                    P[F_BEST_T * fs] = RT.best;
+                    P[F_SEC_T * fs] = RT.sec;
+                    P[F_IDX_T * fs] = __int_as_float(RT.idx);
+                    P[F_Z_T * fs] = M1 ? RT.z * zs1 : RT.z;
+                    P[(REV ? F_B : F_A) * fs] = aa;
+                    P[F_ZH * fs] = zh;
                 }
             }
             // every wave is past its last read of the ring before the next unit's
@@ -499,7 +499,7 @@ struct Wide {
         const int t_rows = t_all < 0 ? 0 : (t_all < z.chunk ? t_all : z.chunk);
         const int n_p = (t_rows + XT - 1) / XT;
         const int G = gridDim.x;
-        const int ns = pass_splits(n_p, a.n_vtiles, G);
+        const int ns = pass_splits(a.sched, t_rows, z.chunk);
         const int64_t n_units = (int64_t)n_p * ns;
         const XLane L = make_lane();
         const int nS = a.ds / XK, nT = 0;
@@ -594,7 +594,7 @@ struct Wide {
         const int t_rows = t_all < 0 ? 0 : (t_all < z.chunk ? t_all : z.chunk);
         const int n_p = (t_rows + XT - 1) / XT;
         const int G = gridDim.x;
-        const int ns = pass_splits(n_p, a.n_vtiles, G);
+        const int ns = pass_splits(a.sched, t_rows, z.chunk);
         const int64_t n_units = (int64_t)n_p * ns;
         const XLane L = make_lane();
         const int nS = a.ds / XK, nT = 0;
@@ -694,9 +694,9 @@ struct Wide {
                 zz += __shfl_xor(zz, 16);
                 zz += __shfl_xor(zz, 32);
                 if (L.g == 0 && tcol[cb] >= 0) {
-                    const int64_t j = (int64_t)z.c0 + tcol[cb];
-                    a.part[(F_BEST_S * MAX_SPLITS + s) * a.pstride + j] = mr[cb * 256];
-                    a.part[(F_Z_S * MAX_SPLITS + s) * a.pstride + j] = zz * 0x1p-15f;
+                    const int64_t j = (int64_t)s * n_p * XT + tcol[cb];
+                    a.part[F_BEST_S * a.fstride + j] = mr[cb * 256];
+                    a.part[F_Z_S * a.fstride + j] = zz * 0x1p-15f;
                 }
             }
             // every DMA landed and every wave is done with the ring before the next

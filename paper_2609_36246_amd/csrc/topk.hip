@@ -83,7 +83,7 @@ topk_select_kernel(ScoreArgs a, TopkWork w) {
     const int64_t g = rm & 0x7fffffffu;
     const int ns = sched->n_splits;
     const int nc = ns * TK_LIST;
-    const int64_t ps = a.pstride;
+    const int64_t fs = a.fstride, ps = sched->pstride;
     for (int m = 0; m < 2; ++m) {
         const int d = m ? a.dt : a.ds;
         const uint16_t *h = (const uint16_t *)(m ? a.ht : a.hs) + g * d;
@@ -100,11 +100,11 @@ topk_select_kernel(ScoreArgs a, TopkWork w) {
         if (lane < ns) {
             for (int e = 0; e < TK_LIST; ++e) {
                 cv[wid][lane * TK_LIST + e] =
-                    a.part[((F_TK + m * TK_FIELDS + e) * MAX_SPLITS + lane) * ps + j];
+                    a.part[(F_TK + m * TK_FIELDS + e) * fs + lane * ps + j];
                 ci[wid][lane * TK_LIST + e] = __float_as_int(
-                    a.part[((F_TK + m * TK_FIELDS + TK_LIST + e) * MAX_SPLITS + lane) * ps + j]);
+                    a.part[(F_TK + m * TK_FIELDS + TK_LIST + e) * fs + lane * ps + j]);
             }
-            fl = a.part[((F_TK + m * TK_FIELDS + 2 * TK_LIST) * MAX_SPLITS + lane) * ps + j];
+            fl = a.part[(F_TK + m * TK_FIELDS + 2 * TK_LIST) * fs + lane * ps + j];
         }
         __builtin_amdgcn_wave_barrier();
         // z16: the 16th largest listed value (lane l < ns walks split l's sorted list)

@@ -1,0 +1,81 @@
+"""GPU tests of the size rules of the scoring kernels: the shapes on either side of a rule,
+each against the fp64 oracle on every row at the acceptance bar.
+"""
+import numpy as np
+import pytest
+import torch
+
+from oracle import olive_oracle as O
+from paper_2609_36246_amd import _lib as L
+from paper_2609_36246_amd import workloads as W
+from tests.gpu_harness import compare, run_hip, say, to_np
+
+pytestmark = pytest.mark.gpu
+
+FORWARD = ("kl", "counts", "logp_s", "logp_t", "am_s", "am_t", "ce")
+
+
+@pytest.fixture(scope="module", autouse=True)
+def gpu():
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    L.load()
+
+
+def custom(name, seed=0, **kw):
+    return W.make_workload(name, seed, device="cuda", spec=W.custom_spec(name=name, **kw))
+
+
+# Few position tiles take more than 32 vocabulary splits (up to 256, one round of the
+# grid). T = positions; at V = 40000 (157 vocabulary tiles) one 256-row tile gives 157
+# splits, two 79 or 128, nine (256-row) 28: both sides of the rule. am ties: the first
+# row's winner is copied to the last vocabulary entry, so that the winner's split and one
+# of the last splits (past the first 32-split mask word) hold the exact tie.
+@pytest.mark.parametrize("T,outs,narrow", [
+    (1, "forward", False), (160, "forward", False), (256, "forward", True),
+    (257, "forward", False), (2048, "forward", False), (2049, "forward", False),
+    (130, "both", False), (200, "student", False), (300, "jsd", False)])
+def test_few_positions_many_splits(T, outs, narrow):
+    say("few positions", T, outs)
+    V = 40000
+    wl = custom("few%d" % T, num_seqs=1, seq_len=T, vocab=V, d_student=64, d_teacher=128,
+                cut_rule=("frac", 0.0, 0.0))
+    z = (wl["h_student"][:1].float() @ wl["w_student"].float())[0]
+    j = int(torch.argmax(z))
+    wl["w_student"][:, V - 1] = wl["w_student"][:, j]
+    o = FORWARD + (("kl_rev",) if outs in ("both", "jsd") else ()) + \
+        (("jsd",) if outs == "jsd" else ())
+    hip = run_hip(wl, outputs=("logp_s", "am_s") if outs == "student" else o,
+                  student_only=outs == "student", narrow=narrow)
+    ns = hip["stats"]["splits"]
+    assert hip["stats"]["kernel"] == "mfma"
+    assert ns > 64 if T <= 300 else ns <= 32, ns
+    assert hip["stats"]["flagged"] >= 1 and hip["am_s"][0] == min(j, V - 1)
+    compare(hip, wl, student_only=outs == "student", label="few-%d-%s" % (T, outs))
+
+
+def test_backward_of_few_rows_many_splits():
+    say("backward of few rows")
+    wl = custom("fewbw", num_seqs=2, seq_len=100, vocab=33000, d_student=128, d_teacher=64,
+                cut_rule=("frac", 0.5, 0.5))
+    T, B = wl["total_positions"], 2
+    f = lambda t: to_np(t).astype(np.float64)   # noqa: E731
+    for w_kl in (0.0, 0.5):
+        ctx = L.olive_score_init(
+            L.make_desc(33000, 128, 64, L.OLIVE_BF16, L.OLIVE_W_DV, 1.0, 1.0, max_positions=T,
+                        max_seqs=B, flags=L.OLIVE_FLAG_BACKWARD), wl["w_student"], wl["w_teacher"])
+        gh = torch.full((T, 128), float("nan"), device="cuda")
+        gw = torch.full((128, 33000), float("nan"), device="cuda")
+        batch = L.make_batch(wl["cu_seqlens"], wl["cut"], wl["targets"], wl["h_student"],
+                             wl["h_teacher"], wl["valid_len"])
+        L.olive_score_backward(ctx, batch, L.make_grad_outputs(1.0, w_kl, gh, gw))
+        torch.cuda.synchronize()
+        L.olive_score_free(ctx)
+        ref = O.backward(f(wl["h_student"]), f(wl["w_student"]), to_np(wl["targets"]),
+                         to_np(wl["cu_seqlens"]), to_np(wl["cut"]), None, f(wl["h_teacher"]),
+                         f(wl["w_teacher"]), w_ce=1.0, w_kl=w_kl)
+        # bf16 rounding of g and its fp32 exponentials (2^-8), fp32 accumulation (K 2^-24)
+        ga, ha, wa = np.abs(ref["g"]), np.abs(f(wl["h_student"])), np.abs(f(wl["w_student"]))
+        bh = (2.0 ** -8 + 33000 * 2.0 ** -24) * (ga @ wa.T) + 1e-6
+        bw = (2.0 ** -8 + T * 2.0 ** -24) * (ha[ref["rows"]].T @ ga) + 1e-6
+        assert np.all(np.abs(to_np(gh)[ref["rows"]] - ref["grad_h"][ref["rows"]]) <= bh)
+        assert np.all(np.abs(to_np(gw) - ref["grad_w"]) <= bw)
