@@ -195,7 +195,6 @@ olive_status run(olive_score_ctx *ctx, const olive_batch *b, const olive_spans *
     const bool has_t = want_t;
     const int64_t T = b->total_positions;
     const int64_t V = d.vocab;
-    const int n_vtiles = (int)((V + 255) / 256);
     // The MFMA kernel streams hidden rows with 16-byte DMAs: it needs 16-byte aligned
     // hidden-state buffers; others take the generic kernel.
     const bool mfma = ctx->mfma_ok && ((uintptr_t)b->h_student & 15) == 0 &&
@@ -215,22 +214,13 @@ olive_status run(olive_score_ctx *ctx, const olive_batch *b, const olive_spans *
     ctx->fwd_lse_ok = false;
 
     olive_status s;
-    int grid = 0;
-    int fixed_splits = 1;
-    int64_t max_units = 0;
-    if (mfma) {
-        grid = ctx->n_cu;
-    } else {
-        int64_t pt = (T + SIMPLE_BT - 1) / SIMPLE_BT;
-        int64_t want = (2048 + pt - 1) / pt;
-        int lim = n_vtiles < MAX_SPLITS ? n_vtiles : MAX_SPLITS;
-        fixed_splits = (int)(want < 1 ? 1 : (want > lim ? lim : want));
-        max_units = pt * fixed_splits;
-    }
+    // a persistent grid: one workgroup per compute unit, or SIMPLE_WG of the generic kernel
+    const int grid = mfma ? ctx->n_cu : SIMPLE_WG * ctx->n_cu;
+    const int vrows = mfma ? MFMA_BV : SIMPLE_VC;
+    const int n_vtiles = (int)((V + vrows - 1) / vrows);
     s = check_hip(launch_prep(*b, spans, region_only, V, ctx->seqbuf, ctx->sched, ctx->err, counts,
-                              wide ? WIDE_BT : (mfma ? MFMA_BT : SIMPLE_BT), mfma ? 0 : 1,
-                              n_vtiles, grid,
-                              fixed_splits, topk ? topk_min_splits(n_vtiles) : 1,
+                              wide ? WIDE_BT : (mfma ? MFMA_BT : SIMPLE_BT), n_vtiles, grid,
+                              topk ? topk_min_splits(n_vtiles) : 1,
                               ctx->fstride, jsd ? MFMA_BT : 0, kOneChunk, st));
     if (s) return s;
     s = check_hip(launch_rowmap(*b, spans, region_only, V, ctx->seqbuf, ctx->sched, ctx->rowmap,
@@ -286,12 +276,12 @@ olive_status run(olive_score_ctx *ctx, const olive_batch *b, const olive_spans *
     else if (mfma)
         s = check_hip(launch_score_mfma(a, has_t, same_scale, has_t && kl_rev, topk, grid, st));
     else
-        s = check_hip(launch_score_simple(a, ctx->bf16, has_t, max_units, st));
+        s = check_hip(launch_score_simple(a, ctx->bf16, has_t, grid, st));
     if (s) return s;
     if (ctx->timing && hipEventRecord(ctx->ev[1][slot], st) != hipSuccess) return OLIVE_E_HIP;
     ctx->n_calls++;
     ctx->last_kernel = wide ? 2 : (mfma ? 0 : 1);
-    ctx->last_grid = mfma ? grid : (int)max_units;
+    ctx->last_grid = grid;
 
     int32_t *flagged = (am_s || (has_t && am_t)) ? ctx->flagged : nullptr;
     s = check_hip(launch_combine(a, ctx->bf16, has_t, same_scale, b->targets, ctx->err, logp_s,
@@ -383,8 +373,8 @@ olive_status run_backward(olive_score_ctx *ctx, const olive_batch *b, const oliv
     // passes take 128-row tiles.
     auto schedule = [&](int tile_rows) {
         olive_status e = check_hip(launch_prep(*b, spans, true, V, ctx->seqbuf, ctx->sched,
-                                               ctx->err, go->counts, tile_rows, 0, n_vtiles,
-                                               grid, 1, 1, ctx->fstride,
+                                               ctx->err, go->counts, tile_rows, n_vtiles,
+                                               grid, 1, ctx->fstride,
                                                wide_dz ? WIDE_BT : MFMA_BT, ch, st));
         if (!e)
             e = check_hip(launch_rowmap(*b, spans, true, V, ctx->seqbuf, ctx->sched, ctx->rowmap,
@@ -612,7 +602,7 @@ bool static_carve(olive_score_ctx *c, char *base) {
     c->wmax_dev = (const float *)take(2 * sizeof(float));
     c->seqbuf = (int32_t *)take((size_t)seqbuf_entries(kStaticMaxSeqs) * sizeof(int32_t));
     c->rowmap = (uint32_t *)take((size_t)P * sizeof(uint32_t));
-    c->fstride = part_field_floats(P, c->n_cu);
+    c->fstride = part_field_floats(P, kStaticMaxVocab, c->n_cu);
     c->part = (float *)take((size_t)NFIELDS * c->fstride * sizeof(float));
     c->logp_tmp = (float *)take((size_t)P * sizeof(float));
     c->flag_cap = (int)P;
@@ -750,7 +740,7 @@ olive_status olive_score_init(olive_score_ctx **out, const olive_score_desc *des
         c->wt = c->has_t ? w_teacher : nullptr;
     }
     const int64_t P = d.max_positions;
-    c->fstride = part_field_floats(P, c->n_cu);
+    c->fstride = part_field_floats(P, V, c->n_cu);
     // One near-tie entry per compacted row at most: the list never drops a flagged row.
     c->flag_cap = (int)P;
     c->fx_window = (int)(P < kFixupWindowRows ? P : kFixupWindowRows);

@@ -122,8 +122,9 @@ enum {
 constexpr int MFMA_BV = 256;     // vocabulary rows per tile (MFMA M)
 constexpr int MFMA_BT = 128;     // positions per tile (MFMA N)
 constexpr int WIDE_BT = 256;     // positions per tile of the 256 x 256 kernel
-constexpr int SIMPLE_BT = 16;    // positions per tile of the generic kernel
-constexpr int SIMPLE_VC = 256;   // vocabulary chunk of the generic kernel
+constexpr int SIMPLE_BT = 64;    // positions per tile of the generic kernel
+constexpr int SIMPLE_VC = 128;   // vocabulary rows per tile of the generic kernel
+constexpr int SIMPLE_WG = 2;     // its workgroups per compute unit (3 fit)
 
 struct ScoreArgs {
     const void *hs, *ht;         // hidden states [T][d] (caller)
@@ -200,12 +201,14 @@ struct GemmArgs {
     int a_prows;
 };
 
-// Floats one partial field holds: MAX_SPLITS splits of every row a call may have, or
-// MAX_SPLITS_FEW splits of few position tiles (tiles x splits <= n_cu, 256 rows a tile at
-// most).
-inline int64_t part_field_floats(int64_t max_positions, int n_cu) {
-    const int64_t all = (max_positions + 255) / 256 * 256 * MAX_SPLITS;
-    const int64_t few = (int64_t)n_cu * 256;
+// Floats one partial field holds: MAX_SPLITS splits of every row a call may have, or up to
+// MAX_SPLITS_FEW (one per 128 vocabulary rows at most) of few position tiles (tiles x
+// splits <= n_cu, 256 rows a tile at most).
+inline int64_t part_field_floats(int64_t max_positions, int64_t vocab, int n_cu) {
+    const int64_t rows = (max_positions + 255) / 256 * 256, vt = (vocab + 127) / 128;
+    const int64_t all = rows * MAX_SPLITS, most = rows * vt;
+    int64_t few = (int64_t)n_cu * 256;
+    few = few < most ? few : most;
     return all > few ? all : few;
 }
 
@@ -215,15 +218,14 @@ hipError_t launch_repack(const void *w_dv, void *w_vd, int64_t d, int64_t V, int
                          hipStream_t st);
 hipError_t launch_prep(const olive_batch &b, const olive_spans *spans, bool region_only,
                        int64_t V, int32_t *seqbuf, Sched *sched, int32_t *err, int64_t *counts,
-                       int tile_rows, int policy, int n_vtiles, int grid, int fixed_splits,
-                       int min_splits, int64_t fstride, int pass_tile, int pass_chunk,
+                       int tile_rows, int n_vtiles, int grid, int min_splits, int64_t fstride, int pass_tile, int pass_chunk,
                        hipStream_t st);
 hipError_t launch_rowmap(const olive_batch &b, const olive_spans *spans, bool region_only,
                          int64_t V, const int32_t *seqbuf,
                          const Sched *sched, uint32_t *rowmap, int32_t *err, float *logp_s,
                          float *logp_t, int32_t *am_s, int32_t *am_t, float *kl, float *kl_rev,
                          float *jsd, float *logp_tmp, const TopkOut &tk, hipStream_t st);
-hipError_t launch_score_simple(const ScoreArgs &a, bool bf16, bool has_t, int64_t max_units,
+hipError_t launch_score_simple(const ScoreArgs &a, bool bf16, bool has_t, int grid,
                                hipStream_t st);
 hipError_t launch_score_mfma(const ScoreArgs &a, bool has_t, bool same_scale, bool rev,
                              bool topk, int grid, hipStream_t st);

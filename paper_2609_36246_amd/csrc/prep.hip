@@ -84,8 +84,8 @@ prep_kernel(const int32_t *__restrict__ cu, const int32_t *__restrict__ cut,
             const int32_t *__restrict__ vlen, int32_t B, int64_t T, int32_t region,
             SpanArgs sp, int32_t region_only, int32_t *__restrict__ seqbuf,
             Sched *__restrict__ sched, int32_t *__restrict__ err, int64_t *__restrict__ counts,
-            int32_t tile_rows, int32_t policy, int32_t n_vtiles, int32_t grid,
-            int32_t fixed_splits, int32_t min_splits, int32_t max_splits, int64_t fstride,
+            int32_t tile_rows, int32_t n_vtiles, int32_t grid, int32_t min_splits,
+            int32_t max_splits, int64_t fstride,
             int32_t pass_tile, int32_t pass_chunk) {
     __shared__ int s_bad, s_badoff;
     __shared__ int s_scan[PREP_THREADS];
@@ -214,10 +214,7 @@ prep_kernel(const int32_t *__restrict__ cu, const int32_t *__restrict__ cut,
     }
     const int t_valid = carry;   // compacted rows: valid, or in-region when region-only
     const int n_p = (t_valid + tile_rows - 1) / tile_rows;
-    int ns = fixed_splits < n_vtiles ? fixed_splits : n_vtiles;
-    if (policy == 0)
-        ns = pick_splits(n_p, n_vtiles, grid, min_splits, max_splits, tile_rows, fstride);
-    if (ns < 1) ns = 1;
+    const int ns = pick_splits(n_p, n_vtiles, grid, min_splits, max_splits, tile_rows, fstride);
     if (tid == 0) {
         cvalid[B] = carry;
         cscored[B] = carry_sc;
@@ -407,15 +404,13 @@ static SpanArgs span_args(const olive_spans *s) {
 
 hipError_t launch_prep(const olive_batch &b, const olive_spans *spans, bool region_only,
                        int64_t V, int32_t *seqbuf, Sched *sched, int32_t *err, int64_t *counts,
-                       int tile_rows, int policy, int n_vtiles, int grid, int fixed_splits,
-                       int min_splits, int64_t fstride, int pass_tile, int pass_chunk,
+                       int tile_rows, int n_vtiles, int grid, int min_splits, int64_t fstride, int pass_tile, int pass_chunk,
                        hipStream_t st) {
     (void)V;
     prep_kernel<<<1, PREP_THREADS, 0, st>>>(b.cu_seqlens, b.cut, b.valid_len, b.num_seqs,
                                             b.total_positions, b.region, span_args(spans),
                                             region_only ? 1 : 0, seqbuf, sched, err, counts,
-                                            tile_rows, policy, n_vtiles, grid, fixed_splits,
-                                            min_splits,
+                                            tile_rows, n_vtiles, grid, min_splits,
                                             min_splits > 1 ? MAX_SPLITS : MAX_SPLITS_FEW,
                                             fstride, pass_tile, pass_chunk);
     return hipGetLastError();

@@ -79,3 +79,41 @@ def test_backward_of_few_rows_many_splits():
         bw = (2.0 ** -8 + T * 2.0 ** -24) * (ha[ref["rows"]].T @ ga) + 1e-6
         assert np.all(np.abs(to_np(gh)[ref["rows"]] - ref["grad_h"][ref["rows"]]) <= bh)
         assert np.all(np.abs(to_np(gw) - ref["grad_w"]) <= bw)
+
+
+# The generic kernel's tiles: 128 vocabulary rows x 64 positions, K in steps of 32 read in
+# groups of 4 elements where width and alignment allow; edges and remainders of each.
+@pytest.mark.parametrize("dtype,T,V,ds,dt,off", [
+    ("f32", 1, 1, 1, 1, 0), ("f32", 64, 128, 32, 64, 0), ("f32", 65, 129, 33, 31, 0),
+    ("f32", 63, 255, 36, 100, 0), ("f32", 130, 20001, 40, 8, 0), ("f32", 700, 300, 5, 67, 1),
+    ("bf16", 70, 200, 64, 64, 0), ("bf16", 65, 1000, 36, 12, 0), ("bf16", 129, 700, 33, 96, 0),
+    ("bf16", 40, 5000, 128, 64, 1)])
+def test_generic_kernel_tile_edges(dtype, T, V, ds, dt, off):
+    say("generic tiles", dtype, T, V, ds, dt, "offset", off)
+    wl = custom("generic", num_seqs=1, seq_len=T, vocab=V, d_student=ds, d_teacher=dt,
+                dtype=dtype, cut_rule=("frac", 0.0, 0.0), target_source="uniform")
+    if off:   # hidden rows one element off the loads' alignment
+        for k in ("h_student", "h_teacher"):
+            b = torch.empty(wl[k].numel() + off, dtype=wl[k].dtype, device="cuda")
+            b[off:] = wl[k].reshape(-1)
+            wl[k] = b[off:].view(wl[k].shape)
+    hip = run_hip(wl, outputs=FORWARD + ("kl_rev",))
+    assert hip["stats"]["kernel"] == "generic"
+    compare(hip, wl, label="generic-%s-%d-%d" % (dtype, T, V))
+    alone = run_hip(wl, outputs=("logp_s", "am_s"), student_only=True)
+    compare(alone, wl, student_only=True, label="generic-student")
+
+
+def test_generic_kernel_nan_and_infinite_rows_stay_their_own():
+    say("generic kernel, rows with NaN and infinite hidden states")
+    wl = custom("generic-nan", num_seqs=1, seq_len=70, vocab=300, d_student=33, d_teacher=64,
+                dtype="f32", cut_rule=("frac", 0.0, 0.0), target_source="uniform")
+    clean = run_hip(wl, outputs=FORWARD)
+    wl["h_student"][3, 5] = float("nan")
+    wl["h_student"][66, 7] = float("inf")
+    hip = run_hip(wl, outputs=FORWARD)
+    assert np.all(np.isnan(hip["logp_s"][[3, 66]])) and np.all(np.isnan(hip["kl"][[3, 66]]))
+    keep = np.setdiff1d(np.arange(70), [3, 66])
+    for k in ("logp_s", "logp_t", "kl", "am_s", "am_t"):
+        np.testing.assert_array_equal(hip[k][keep], clean[k][keep], err_msg=k)
+    np.testing.assert_array_equal(hip["logp_t"], clean["logp_t"])
