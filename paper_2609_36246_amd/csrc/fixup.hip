@@ -13,7 +13,7 @@
 //   z_v + e_v >= theta = (fp32 max of the scoring pass) - (its own bound),
 // are evaluated in fp64 and the largest wins, lowest index first.
 //
-// Work items are (batch of up to FB flagged rows, vocabulary chunk, model): the
+// Work items are (batch of up to FB flagged rows, vocabulary chunk or part of one, model): the
 // batch's hidden rows are staged in LDS and every weight row of the chunk is read
 // once for all of them, so W streams from HBM once per batch rather than once per
 // flagged row. Per-chunk winners are merged per row in a fixed order (phase 2).
@@ -32,6 +32,22 @@ constexpr int FX_THREADS = 256;
 constexpr int FX_GROUPS = FX_THREADS / 8;   // 8 lanes per weight row
 constexpr int FX_MAXB = 8;              // flagged rows per pass over W
 constexpr int FX_LDS = 65536;           // bytes of staged hidden rows per work item
+
+constexpr int FX_GRID = 1024;           // workgroups of the scan
+constexpr int FX_SUB = 8;               // parts a chunk may be cut into
+
+// Parts every chunk is cut into for nf flagged rows in n_batches batches: enough work items
+// for the grid (a few flagged rows at V = 32000 give 64 items otherwise, on 256 compute
+// units), while the nf x chunks x parts results fit the window's scratch of cap x chunks.
+// An fp32 call of 499 positions, V = 32000, d 1024 + 2048 with a flagged row: 1.75 ms with
+// whole chunks of both models, 1.00 ms with parts of the flagged one.
+__device__ __forceinline__ int fx_parts(int nf, int n_batches, int n_chunks, int cap) {
+    int k = 1;
+    while (k < FX_SUB && (int64_t)n_batches * n_chunks * 2 * k < FX_GRID &&
+           (int64_t)2 * k * nf <= cap)
+        k *= 2;
+    return k;
+}
 
 struct FxResult {
     double val;
@@ -109,13 +125,18 @@ fixup_scan_kernel(ScoreArgs a, const int32_t *__restrict__ flagged, int f_base, 
     const int nf = nf_all < 0 ? 0 : (nf_all < cap ? nf_all : cap);
     flagged += 4 * (int64_t)f_base;
     const int n_batches = (nf + FB - 1) / FB;
-    const int64_t n_items = (int64_t)n_batches * n_chunks * 2;
+    const int parts = fx_parts(nf, n_batches, n_chunks, cap);
+    const int n_parts = n_chunks * parts, rows = FX_CHUNK / parts;
+    const int64_t n_items = (int64_t)n_batches * n_parts * 2;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g8 = lane & 7;
     for (int64_t item = blockIdx.x; item < n_items; item += gridDim.x) {
         const int m = (int)(item & 1);
         const int64_t rest = item >> 1;
-        const int c = (int)(rest % n_chunks);
-        const int f0 = (int)(rest / n_chunks) * FB;
+        const int c = (int)(rest % n_parts);
+        const int f0 = (int)(rest / n_parts) * FB;
+        int any = 0;   // a batch without a row flagged for this model is not read
+        for (int i = f0; i < f0 + FB && i < nf; ++i) any |= flagged[4 * i + 1] & (1 << m);
+        if (!any) continue;
         const int d = m ? a.dt : a.ds;
         const E *H = (const E *)(m ? a.ht : a.hs);
         const E *W = (const E *)(m ? a.wt : a.ws);
@@ -173,9 +194,10 @@ fixup_scan_kernel(ScoreArgs a, const int32_t *__restrict__ flagged, int f_base, 
         // 8 lanes per weight row: each pass of a group reads 128 contiguous bytes of its
         // row (bf16), so a wavefront reads 8 rows at a time, coalesced.
         const bool vec = (d & 63) == 0 && (((uintptr_t)W & 15) == 0);
-        const int v_end = (c + 1) * FX_CHUNK < a.V ? (c + 1) * FX_CHUNK : a.V;
-        for (int v0 = c * FX_CHUNK; v0 < v_end; v0 += FX_GROUPS) {
-            const int v = v0 + (tid >> 3);
+        const int64_t v_lim = ((int64_t)c + 1) * rows;
+        const int v_end = v_lim < a.V ? (int)v_lim : a.V;
+        for (int64_t v0 = (int64_t)c * rows; v0 < v_end; v0 += FX_GROUPS) {
+            const int v = (int)v0 + (tid >> 3);
             const bool ok = v < v_end;
             const E *wr = W + (int64_t)(ok ? v : v_end - 1) * d;
             float z[FB];
@@ -203,9 +225,7 @@ fixup_scan_kernel(ScoreArgs a, const int32_t *__restrict__ flagged, int f_base, 
                     }
                 }
             } else if (vec) {
-                for (int k = g8 * 8; k < d; k += 64) {
-                    float x[8];
-                    load8(wr + k, x);
+                auto dotf = [&](int k, const float (&x)[8]) {
 #pragma unroll
                     for (int i = 0; i < FB; ++i) {
                         float hv[8];
@@ -213,6 +233,19 @@ fixup_scan_kernel(ScoreArgs a, const int32_t *__restrict__ flagged, int f_base, 
 #pragma unroll
                         for (int q = 0; q < 8; ++q) z[i] = fmaf(hv[q], x[q], z[i]);
                     }
+                };
+                int k = g8 * 8;
+                for (; k + 3 * 64 < d; k += 4 * 64) {   // 8 loads in flight, as above
+                    float x[4][8];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) load8(wr + k + j * 64, x[j]);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) dotf(k + j * 64, x[j]);
+                }
+                for (; k < d; k += 64) {
+                    float x[8];
+                    load8(wr + k, x);
+                    dotf(k, x);
                 }
             } else {
                 for (int k = g8; k < d; k += 8) {
@@ -268,14 +301,19 @@ fixup_scan_kernel(ScoreArgs a, const int32_t *__restrict__ flagged, int f_base, 
     }
 }
 
-__global__ void __launch_bounds__(64)
+// One wavefront per flagged row: the best of its parts' winners (lower index first among
+// equals, as in vocabulary order).
+__global__ void __launch_bounds__(256)
 fixup_merge_kernel(ScoreArgs a, const int32_t *__restrict__ flagged, int f_base, int cap,
-                   int n_chunks, const FxResult *__restrict__ res, int32_t *__restrict__ am_s,
+                   int n_chunks, int fb, const FxResult *__restrict__ res,
+                   int32_t *__restrict__ am_s,
                    int32_t *__restrict__ am_t) {
     const int nf_all = a.sched->n_flagged - f_base;
     const int nf = nf_all < 0 ? 0 : (nf_all < cap ? nf_all : cap);
     flagged += 4 * (int64_t)f_base;
-    for (int f = blockIdx.x * 64 + threadIdx.x; f < nf; f += gridDim.x * 64) {
+    const int lane = threadIdx.x & 63;
+    const int n_parts = n_chunks * fx_parts(nf, (nf + fb - 1) / fb, n_chunks, cap);
+    for (int f = blockIdx.x * 4 + (threadIdx.x >> 6); f < nf; f += gridDim.x * 4) {
         const int32_t j = flagged[4 * f];
         const int32_t mask = flagged[4 * f + 1];
         const int64_t g = a.rowmap[j] & 0x7fffffffu;
@@ -283,11 +321,16 @@ fixup_merge_kernel(ScoreArgs a, const int32_t *__restrict__ flagged, int f_base,
             if (!(mask & (1 << m))) continue;
             double bv = -__builtin_inf();
             int bi = 0x7fffffff;
-            for (int c = 0; c < n_chunks; ++c) {     // chunk order = vocabulary order
+            for (int c = lane; c < n_parts; c += 64) {
                 const FxResult r = res[((int64_t)c * nf + f) * 2 + m];
-                if (r.val > bv) { bv = r.val; bi = r.idx; }
+                if (r.val > bv || (r.val == bv && r.idx < bi)) { bv = r.val; bi = r.idx; }
             }
-            if (bi != 0x7fffffff) {
+            for (int off = 32; off > 0; off >>= 1) {
+                const double ov = __shfl_xor(bv, off);
+                const int oi = __shfl_xor(bi, off);
+                if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
+            }
+            if (lane == 0 && bi != 0x7fffffff) {
                 int32_t *am = m ? am_t : am_s;
                 if (am) am[g] = bi;
             }
@@ -330,7 +373,7 @@ template <typename E, int FB>
 static void launch_scan(const ScoreArgs &a, const int32_t *flagged, int f_base, int cap,
                         int n_chunks, size_t lds, const float *wn_s, const float *wn_t,
                         FxResult *res, hipStream_t st) {
-    fixup_scan_kernel<E, FB><<<1024, FX_THREADS, lds, st>>>(a, flagged, f_base, cap, n_chunks,
+    fixup_scan_kernel<E, FB><<<FX_GRID, FX_THREADS, lds, st>>>(a, flagged, f_base, cap, n_chunks,
                                                              wn_s, wn_t, res);
 }
 
@@ -364,7 +407,7 @@ hipError_t launch_fixup_impl(const ScoreArgs &a, bool bf16, const int32_t *flagg
         launch_scan_fb<float>(fb, a, flagged, f_base, cap, n_chunks, lds, wn_s, wn_t, res, st);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    fixup_merge_kernel<<<64, 64, 0, st>>>(a, flagged, f_base, cap, n_chunks, res, am_s, am_t);
+    fixup_merge_kernel<<<64, 256, 0, st>>>(a, flagged, f_base, cap, n_chunks, fb, res, am_s, am_t);
     return hipGetLastError();
 }
 

@@ -81,7 +81,7 @@ constexpr int SPLIT_WORDS = MAX_SPLITS_FEW / 32;
 constexpr int kOneChunk = 0x7fffffff;   // a pass that takes the scored rows in one chunk
 
 // Device-side schedule of one call, written by the preparation kernel.
-struct Sched {
+struct alignas(16) Sched {
     int32_t t_valid;    // compacted rows: valid positions, or only the in-region ones when
                         // the call restricts every output to the region
     int32_t n_ptiles;   // ceil(t_valid / tile_rows) for the kernel in use

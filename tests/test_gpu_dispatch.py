@@ -117,3 +117,19 @@ def test_generic_kernel_nan_and_infinite_rows_stay_their_own():
     for k in ("logp_s", "logp_t", "kl", "am_s", "am_t"):
         np.testing.assert_array_equal(hip[k][keep], clean[k][keep], err_msg=k)
     np.testing.assert_array_equal(hip["logp_t"], clean["logp_t"])
+
+
+# The generic path's exact re-decision cuts its vocabulary chunks by the flagged rows'
+# count: 1 row, a batch and one more (8 parts a chunk), and enough for whole chunks.
+@pytest.mark.parametrize("dtype,ties", [("f32", 1), ("f32", 9), ("bf16", 9), ("f32", 400)])
+def test_generic_exact_decision_parts(dtype, ties):
+    say("generic re-decision", dtype, ties)
+    V, T = 20003, 420
+    wl = custom("parts", num_seqs=1, seq_len=T, vocab=V, d_student=72, d_teacher=33, dtype=dtype,
+                cut_rule=("frac", 0.0, 0.0), target_source="uniform")
+    z = wl["h_student"][:ties].float() @ wl["w_student"].float()
+    for j in sorted(set(torch.argmax(z, dim=1).tolist())):
+        wl["w_student"][:, (j + V // 2) % V] = wl["w_student"][:, j]   # an exact tie
+    hip = run_hip(wl, outputs=FORWARD)
+    assert hip["stats"]["kernel"] == "generic" and hip["stats"]["flagged"] >= min(ties, 300)
+    compare(hip, wl, label="parts-%s-%d" % (dtype, ties))
