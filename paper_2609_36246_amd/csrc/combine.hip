@@ -236,6 +236,7 @@ combine_kernel(ScoreArgs a, int same_scale, const int32_t *__restrict__ targets,
     }
     if (fl && flagged) {
         int q = atomicAdd(&sched->n_flagged, 1);
+        atomicOr(&sched->fl_models, (uint32_t)fl);
         if (q < flag_cap) {
             flagged[4 * q] = (int32_t)j;
             flagged[4 * q + 1] = fl;

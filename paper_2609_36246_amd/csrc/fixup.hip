@@ -92,18 +92,42 @@ __device__ __forceinline__ void dot8(const uint16_t *hrows, int d, int k, const 
         z[i] = dot2bf(hq.w, wq.w, z[i]);
     }
 }
-// Squared L2 norm of every weight row (init only): one wavefront per row.
+// L2 norm of every weight row, rounded up: one wavefront per row, 16 bytes a lane where
+// rows allow. With `sched` (a call without a context, whose weights no init has seen) only
+// if a row is flagged for the model.
 template <typename E>
 __global__ void __launch_bounds__(256)
-row_norm_kernel(const E *__restrict__ w, int64_t V, int d, float *__restrict__ out) {
+row_norm_kernel(const E *__restrict__ w, int64_t V, int d, float *__restrict__ out,
+                const Sched *__restrict__ sched, uint32_t model_bit) {
+    if (sched && !(sched->fl_models & model_bit)) return;
     const int lane = threadIdx.x & 63;
+    constexpr int N = 16 / sizeof(E);   // elements per load
+    const bool vec = d % N == 0 && ((uintptr_t)w & 15) == 0;
     for (int64_t v = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); v < V;
          v += (int64_t)gridDim.x * 4) {
         const E *r = w + v * d;
         double acc = 0.0;
-        for (int k = lane; k < d; k += 64) {
-            const double x = load_elem(r, k);
-            acc += x * x;
+        if (vec) {
+            for (int k = lane * N; k < d; k += 64 * N) {
+                const uint4 q = *(const uint4 *)(r + k);
+                const uint32_t x[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    if constexpr (sizeof(E) == 4) {
+                        const double y = __uint_as_float(x[e]);
+                        acc += y * y;
+                    } else {
+                        const double lo = __uint_as_float(x[e] << 16);
+                        const double hi = __uint_as_float(x[e] & 0xffff0000u);
+                        acc += lo * lo + hi * hi;
+                    }
+                }
+            }
+        } else {
+            for (int k = lane; k < d; k += 64) {
+                const double x = load_elem(r, k);
+                acc += x * x;
+            }
         }
         for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
         if (lane == 0) out[v] = (float)sqrt(acc) * 1.0001f;   // rounded up
@@ -338,34 +362,15 @@ fixup_merge_kernel(ScoreArgs a, const int32_t *__restrict__ flagged, int f_base,
     }
 }
 
-// out[0] = (1 + 2^-10) max_v wn[v]: the largest weight-row norm with the margin the
-// rounding bounds use (one workgroup; max is exact in any order).
-__global__ void __launch_bounds__(1024)
-max_norm_kernel(const float *__restrict__ wn, int64_t V, float *__restrict__ out) {
-    __shared__ float red[1024];
-    float m = 0.f;
-    for (int64_t v = threadIdx.x; v < V; v += 1024) m = fmaxf(m, wn[v]);
-    red[threadIdx.x] = m;
-    __syncthreads();
-    for (int off = 512; off > 0; off >>= 1) {
-        if ((int)threadIdx.x < off) red[threadIdx.x] = fmaxf(red[threadIdx.x], red[threadIdx.x + off]);
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) out[0] = red[0] * (1.0f + 0x1p-10f);
-}
-
-hipError_t launch_max_norm(const float *wn, int64_t V, float *out, hipStream_t st) {
-    max_norm_kernel<<<1, 1024, 0, st>>>(wn, V, out);
-    return hipGetLastError();
-}
-
 hipError_t launch_row_norms(const void *w, int64_t V, int d, bool bf16, float *out,
-                            hipStream_t st) {
+                            const Sched *sched, uint32_t model_bit, hipStream_t st) {
     const int64_t blocks = (V + 3) / 4 < 4096 ? (V + 3) / 4 : 4096;
     if (bf16)
-        row_norm_kernel<uint16_t><<<(unsigned)blocks, 256, 0, st>>>((const uint16_t *)w, V, d, out);
+        row_norm_kernel<uint16_t><<<(unsigned)blocks, 256, 0, st>>>((const uint16_t *)w, V, d, out,
+                                                              sched, model_bit);
     else
-        row_norm_kernel<float><<<(unsigned)blocks, 256, 0, st>>>((const float *)w, V, d, out);
+        row_norm_kernel<float><<<(unsigned)blocks, 256, 0, st>>>((const float *)w, V, d, out, sched,
+                                                           model_bit);
     return hipGetLastError();
 }
 

@@ -40,6 +40,8 @@ struct olive_score_ctx {
     float *wn_s = nullptr, *wn_t = nullptr;     // weight-row L2 norms (rounding bounds)
     float wmax_s = 0.f, wmax_t = 0.f;           // their maxima
     const float *wmax_dev = nullptr;            // or the maxima in device memory
+    bool no_init = false;                       // a call without a context: its weights' norms
+                                                // are formed by its own kernels
     int32_t *err = nullptr;
     void *tk_buf = nullptr;                     // top-K workspace (OLIVE_FLAG_TOPK)
     TopkWork tkw = {};
@@ -274,7 +276,8 @@ olive_status run(olive_score_ctx *ctx, const olive_batch *b, const olive_spans *
     if (wide)
         s = check_hip(launch_score_wide(a, same_scale, has_t, wide_rev, grid, st));
     else if (mfma)
-        s = check_hip(launch_score_mfma(a, has_t, same_scale, has_t && kl_rev, topk, grid, st));
+        s = check_hip(launch_score_mfma(a, has_t, same_scale, has_t && kl_rev, topk,
+                                        ctx->no_init, grid, st));
     else
         s = check_hip(launch_score_simple(a, ctx->bf16, has_t, grid, st));
     if (s) return s;
@@ -301,6 +304,12 @@ olive_status run(olive_score_ctx *ctx, const olive_batch *b, const olive_spans *
         if (mfma)
             s = check_hip(launch_argmax_fix(a, flagged, ctx->flag_cap, ctx->fxq, am_s,
                                             has_t ? am_t : nullptr, st));
+        else if (ctx->no_init &&   // the rounding bounds of the flagged rows' candidates
+                 (launch_row_norms(a.ws, V, a.ds, ctx->bf16, ctx->wn_s, ctx->sched, 1u, st) !=
+                      hipSuccess ||
+                  launch_row_norms(a.wt, V, a.dt, ctx->bf16, ctx->wn_t, ctx->sched, 2u, st) !=
+                      hipSuccess))
+            return OLIVE_E_HIP;
         else
             // windows over the flagged list: at most one entry per compacted row
             for (int64_t f0 = 0; f0 < T && !s; f0 += ctx->fx_window)
@@ -429,7 +438,8 @@ olive_status run_backward(olive_score_ctx *ctx, const olive_batch *b, const oliv
                                              ctx->sched, ctx->hp_rows, ctx->hp_t, st));
             if (!s) s = check_hip(launch_score_wide(a, same_scale, has_t, false, grid, st));
         } else {
-            s = check_hip(launch_score_mfma(a, has_t, same_scale, false, false, grid, st));
+            s = check_hip(launch_score_mfma(a, has_t, same_scale, false, false, false, grid,
+                                            st));
         }
         if (s) return s;
         s = check_hip(launch_combine(a, true, has_t, same_scale, b->targets, ctx->err, nullptr,
@@ -599,7 +609,8 @@ bool static_carve(olive_score_ctx *c, char *base) {
     };
     c->sched = (Sched *)take(sizeof(Sched));
     c->err = (int32_t *)take(sizeof(int32_t));
-    c->wmax_dev = (const float *)take(2 * sizeof(float));
+    c->wmax_dev = c->sched->wmax;
+    c->no_init = true;
     c->seqbuf = (int32_t *)take((size_t)seqbuf_entries(kStaticMaxSeqs) * sizeof(int32_t));
     c->rowmap = (uint32_t *)take((size_t)P * sizeof(uint32_t));
     c->fstride = part_field_floats(P, kStaticMaxVocab, c->n_cu);
@@ -654,16 +665,8 @@ olive_status olive_kl_masked_static(const olive_score_desc *desc, const void *w_
     c.has_t = true;
     c.mfma_ok = mfma_applies(d, w_student, w_teacher);
     if (!static_carve(&c, sd->base)) return OLIVE_E_LIMIT;
-    hipStream_t st = (hipStream_t)hip_stream;
-    // the weight-row norms and their maxima bound the rounding of the near-tie decisions
-    float *wmax = const_cast<float *>(c.wmax_dev);
-    if (launch_row_norms(c.ws, d.vocab, d.d_student, c.bf16, c.wn_s, st) != hipSuccess ||
-        launch_row_norms(c.wt, d.vocab, d.d_teacher, c.bf16, c.wn_t, st) != hipSuccess ||
-        launch_max_norm(c.wn_s, d.vocab, wmax, st) != hipSuccess ||
-        launch_max_norm(c.wn_t, d.vocab, wmax + 1, st) != hipSuccess)
-        return OLIVE_E_HIP;
     return run(&c, b, nullptr, kl, nullptr, counts, logp_student, logp_teacher, argmax_student,
-               argmax_teacher, ce_per_seq, st);
+               argmax_teacher, ce_per_seq, (hipStream_t)hip_stream);
 }
 
 const char *olive_status_string(olive_status s) {
@@ -799,8 +802,8 @@ olive_status olive_score_init(olive_score_ctx **out, const olive_score_desc *des
     if (!s) s = dev_alloc(&c->wn_s, (size_t)V * sizeof(float));
     if (!s && c->has_t) s = dev_alloc(&c->wn_t, (size_t)V * sizeof(float));
     if (s) { release(c); return s; }
-    if (launch_row_norms(c->ws, V, d.d_student, c->bf16, c->wn_s, st) != hipSuccess ||
-        (c->has_t && launch_row_norms(c->wt, V, d.d_teacher, c->bf16, c->wn_t, st) != hipSuccess)) {
+    if (launch_row_norms(c->ws, V, d.d_student, c->bf16, c->wn_s, nullptr, 0u, st) != hipSuccess ||
+        (c->has_t && launch_row_norms(c->wt, V, d.d_teacher, c->bf16, c->wn_t, nullptr, 0u, st) != hipSuccess)) {
         release(c);
         return OLIVE_E_HIP;
     }

@@ -89,6 +89,9 @@ struct alignas(16) Sched {
     int32_t n_units;    // n_ptiles * n_splits
     int64_t n_scored;   // in-region valid positions
     int32_t n_flagged;  // rows queued for the near-tie argmax re-decision
+    uint32_t fl_models; // the models (bits) of which a row is flagged
+    float wmax[2];      // a call without a context: the largest weight-row norms, formed by
+                        // its scoring pass
     int32_t pstride;    // floats from one split's partials to the next: n_ptiles tiles of rows
     int32_t pass_splits[2];   // vocabulary splits of a pass over the scored rows: of a full
                               // chunk of them, and of the last, shorter one
@@ -228,7 +231,7 @@ hipError_t launch_rowmap(const olive_batch &b, const olive_spans *spans, bool re
 hipError_t launch_score_simple(const ScoreArgs &a, bool bf16, bool has_t, int grid,
                                hipStream_t st);
 hipError_t launch_score_mfma(const ScoreArgs &a, bool has_t, bool same_scale, bool rev,
-                             bool topk, int grid, hipStream_t st);
+                             bool topk, bool norms, int grid, hipStream_t st);
 hipError_t launch_score_wide(const ScoreArgs &a, bool same_scale, bool has_t, bool rev,
                              int grid, hipStream_t st);
 hipError_t launch_score_wide_dz(const ScoreArgs &a, const DzArgs &z, int grid, hipStream_t st);
@@ -269,8 +272,7 @@ hipError_t launch_fixup_impl(const ScoreArgs &a, bool bf16, const int32_t *flagg
                              int cap, void *scratch, const float *wn_s, const float *wn_t,
                              int32_t *am_s, int32_t *am_t, hipStream_t st);
 hipError_t launch_row_norms(const void *w, int64_t V, int d, bool bf16, float *out,
-                            hipStream_t st);
-hipError_t launch_max_norm(const float *wn, int64_t V, float *out, hipStream_t st);
+                            const Sched *sched, uint32_t model_bit, hipStream_t st);
 int fixup_chunks(int64_t V);
 size_t fixup_result_bytes();
 hipError_t launch_ce(const olive_batch &b, const olive_spans *spans, const int32_t *seqbuf,

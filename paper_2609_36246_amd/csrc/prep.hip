@@ -124,6 +124,7 @@ prep_kernel(const int32_t *__restrict__ cu, const int32_t *__restrict__ cut,
             atomicOr(err, ERR_CU);
             sched->t_valid = 0; sched->n_ptiles = 0; sched->n_splits = 1; sched->n_units = 0;
             sched->n_scored = 0; sched->n_flagged = 0; sched->cu_bad = 1;
+            sched->fl_models = 0u; sched->wmax[0] = 0.f; sched->wmax[1] = 0.f;
             sched->n_tkq[0] = 0; sched->n_tkq[1] = 0; sched->n_tk_fb = 0;
             sched->n_fxq[0] = 0; sched->n_fxq[1] = 0; sched->n_fx_fb = 0;
             sched->pstride = 0;
@@ -224,6 +225,7 @@ prep_kernel(const int32_t *__restrict__ cu, const int32_t *__restrict__ cut,
         sched->n_units = n_p * ns;
         sched->n_scored = scored;
         sched->n_flagged = 0;
+        sched->fl_models = 0u; sched->wmax[0] = 0.f; sched->wmax[1] = 0.f;
         sched->n_tkq[0] = 0; sched->n_tkq[1] = 0; sched->n_tk_fb = 0;
         sched->n_fxq[0] = 0; sched->n_fxq[1] = 0; sched->n_fx_fb = 0;
         sched->pstride = n_p * tile_rows;

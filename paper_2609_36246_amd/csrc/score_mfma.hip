@@ -70,7 +70,28 @@ __device__ __forceinline__ uint32_t umed3(uint32_t a, uint32_t b, uint32_t c) {
     return lo > m ? lo : m;
 }
 
-template <bool HAS_T, bool SAME, bool REV, bool TOPK>
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+
+// n plus the sum of squares of elements 4 half .. 4 half + 3 of an operand fragment.
+template <int HALF>
+__device__ __forceinline__ float add_squares(const bf16x8 &x, float n) {
+#pragma unroll
+    for (int e = 4 * HALF; e < 4 * HALF + 4; e += 2) {
+        const bf16x2 p = {x[e], x[e + 1]};
+        n = __builtin_amdgcn_fdot2_f32_bf16(p, p, n, false);
+    }
+    return n;
+}
+
+// NORMS: also the largest weight-row norms of both models, which bound the rounding of the
+// near-tie decisions of a call without a context (whose caller's weights no init has
+// seen). Every position tile's units read every weight row; in vocabulary tile t those of
+// position tile t mod (their number) add the squares of their weight fragments, 2 dot
+// products after each MFMA, instead of a pass of its own over both matrices (1.5 GB at
+// V = 151936, d 1536 + 3584: 0.92 ms of a call of 771 positions). The dot products lengthen
+// a tile's sweep by some 30 %, so they are spread over the position tiles: 1.47 ms in the
+// kernel without them, 1.85 ms with position tile 0 taking them all, 1.58 ms spread.
+template <bool HAS_T, bool SAME, bool REV, bool TOPK, bool NORMS = false>
 struct Kernel {
     // Issue cursor: the next step to prefetch. Wave-uniform: its model block (vocabulary
     // tile vt, model m, step kk of the block's cnt), the W tile pointer at the step's K
@@ -175,13 +196,18 @@ struct Kernel {
         for (int cb = 0; cb < 2; ++cb) F.B[cb] = *(const bf16x8 *)(hb + cb * 32 * ROWB);
     }
 
-    static __device__ __forceinline__ void mma(const Frag &F, floatx16 (&acc)[4][2]) {
+    // NORM: nsq[vb] also takes the squares of the lane's elements of row block vb.
+    template <bool NORM>
+    static __device__ __forceinline__ void mma(const Frag &F, floatx16 (&acc)[4][2],
+                                               float (&nsq)[4]) {
 #pragma unroll
-        for (int vb = 0; vb < 4; ++vb)
+        for (int vb = 0; vb < 4; ++vb) {
 #pragma unroll
             for (int cb = 0; cb < 2; ++cb)
                 acc[vb][cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(F.A[vb], F.B[cb],
                                                                       acc[vb][cb], 0, 0, 0);
+            if constexpr (NORM) nsq[vb] = add_squares<1>(F.A[vb], add_squares<0>(F.A[vb], nsq[vb]));
+        }
     }
 
     template <int QB, int QE>
@@ -196,14 +222,16 @@ struct Kernel {
     // between them. Each 1 KB DMA holds the CU's address path for about 16 cycles, so
     // the refill is spread over the whole step: issued in a burst, the DMAs back up
     // and stall the wave in front of its next MFMA.
-    template <int Q0, int NQ>
+    template <bool NORM, int Q0, int NQ>
     static __device__ __forceinline__ void mma_issue(const Frag &F, floatx16 (&acc)[4][2],
-                                                     const Cursor &C, uint32_t lw, uint32_t lh) {
+                                                     float (&nsq)[4], const Cursor &C,
+                                                     uint32_t lw, uint32_t lh) {
 #define OLIVE_MI(J_, VB_, CB_)                                                             \
         __builtin_amdgcn_sched_barrier(0);                                               \
         acc[VB_][CB_] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(F.A[VB_], F.B[CB_],        \
                                                                 acc[VB_][CB_], 0, 0, 0); \
         __builtin_amdgcn_sched_barrier(0);                                               \
+        if constexpr (NORM) nsq[VB_] = add_squares<CB_>(F.A[VB_], nsq[VB_]);               \
         dmas<Q0 + ((J_) * NQ + 7) / 8, Q0 + ((J_) * NQ + NQ + 7) / 8>(C, lw, lh);
         OLIVE_MI(0, 0, 0)
         OLIVE_MI(1, 0, 1)
@@ -236,9 +264,10 @@ struct Kernel {
     // holds this step's last sub-step, still to be run. Every step issues its 12 DMAs
     // (past the end of a unit, those of its last step again), so no DMA sits under a
     // branch.
-    template <bool PEND>
+    template <bool PEND, bool NORM>
     static __device__ __forceinline__ void step(const ScoreArgs &a, const Lane &L, Cursor &C,
-                                                int st, floatx16 (&acc)[4][2], Frag &P) {
+                                                int st, floatx16 (&acc)[4][2], float (&nsq)[4],
+                                                Frag &P) {
         const int pv = st == 0 ? NST - 1 : st - 1;
         turn(C, a, L);
         arrive();
@@ -247,26 +276,26 @@ struct Kernel {
         read_frag<0>(L, st, F0);
         __builtin_amdgcn_sched_barrier(0);
         if (PEND) {
-            mma_issue<0, 3>(P, acc, C, lw, lh);
+            mma_issue<NORM, 0, 3>(P, acc, nsq, C, lw, lh);
             read_frag<1>(L, st, F1);
             __builtin_amdgcn_sched_barrier(0);
-            mma_issue<3, 3>(F0, acc, C, lw, lh);
+            mma_issue<NORM, 3, 3>(F0, acc, nsq, C, lw, lh);
             read_frag<2>(L, st, F2);
             __builtin_amdgcn_sched_barrier(0);
-            mma_issue<6, 3>(F1, acc, C, lw, lh);
+            mma_issue<NORM, 6, 3>(F1, acc, nsq, C, lw, lh);
             read_frag<3>(L, st, P);
             __builtin_amdgcn_sched_barrier(0);
-            mma_issue<9, 3>(F2, acc, C, lw, lh);
+            mma_issue<NORM, 9, 3>(F2, acc, nsq, C, lw, lh);
         } else {
             read_frag<1>(L, st, F1);
             __builtin_amdgcn_sched_barrier(0);
-            mma_issue<0, 4>(F0, acc, C, lw, lh);
+            mma_issue<NORM, 0, 4>(F0, acc, nsq, C, lw, lh);
             read_frag<2>(L, st, F2);
             __builtin_amdgcn_sched_barrier(0);
-            mma_issue<4, 4>(F1, acc, C, lw, lh);
+            mma_issue<NORM, 4, 4>(F1, acc, nsq, C, lw, lh);
             read_frag<3>(L, st, P);
             __builtin_amdgcn_sched_barrier(0);
-            mma_issue<8, 4>(F2, acc, C, lw, lh);
+            mma_issue<NORM, 8, 4>(F2, acc, nsq, C, lw, lh);
         }
         advance(C);
     }
@@ -277,10 +306,13 @@ struct Kernel {
     // through the cursor, across block and tile ends. LOCK: phase-lock the XCD's
     // workgroups at tile starts (the scoring pass; the backward's passes, whose tile ends
     // hold more live state, leave it off).
+    // NORMS: in the tiles vt with vt mod n_p = p, wsq[model] rises to the largest squared norm
+    // of the lane's weight rows.
     template <bool LOCK, class TileEnd>
     static __device__ __forceinline__ void sweep(const ScoreArgs &a, const Lane &L, int vt0,
                                                  int vt1, int nS, int nT,
                                                  floatx16 (&accS)[4][2], floatx16 (&accT)[4][2],
+                                                 int p, int n_p, float (&wsq)[2],
                                                  TileEnd &&tile_end) {
         Cursor C;
         C.vt1 = vt1;
@@ -297,17 +329,22 @@ struct Kernel {
         int st = 0;   // ring stage of the current step
         // A model block of COUNT_ steps: the first step has no pending sub-step, the
         // block's last sub-step runs after the loop.
-#define OLIVE_STEPS(ACC_, COUNT_)                                                        \
+#define OLIVE_STEPS(ACC_, COUNT_, MODEL_, NORM)                                          \
         {                                                                                \
             Frag P;                                                                      \
-            step<false>(a, L, C, st, ACC_, P);                                           \
+            float nsq[4] = {0.f, 0.f, 0.f, 0.f};                                         \
+            step<false, NORM>(a, L, C, st, ACC_, nsq, P);                                \
             st = st + 1 == NST ? 0 : st + 1;                                             \
             for (int k = 1; k < (COUNT_); ++k) {                                         \
-                step<true>(a, L, C, st, ACC_, P);                                        \
+                step<true, NORM>(a, L, C, st, ACC_, nsq, P);                             \
                 st = st + 1 == NST ? 0 : st + 1;                                         \
             }                                                                            \
-            mma(P, ACC_);                                                                \
+            mma<NORM>(P, ACC_, nsq);                                                     \
             __builtin_amdgcn_sched_barrier(0);                                           \
+            if constexpr (NORM) {                                                        \
+                for (int vb = 0; vb < 4; ++vb)                                           \
+                    wsq[MODEL_] = fmaxf(wsq[MODEL_], nsq[vb] + __shfl_xor(nsq[vb], 32)); \
+            }                                                                            \
         }
         // Phase lock of the XCD's workgroups (phase_lock.hpp); the first two tiles of a
         // unit only measure the period.
@@ -320,8 +357,13 @@ struct Kernel {
             // V; its rows below vt*BV were covered by the previous tile.
             const int row0 = (vt * BV < a.V - BV) ? vt * BV : a.V - BV;
             zero_acc(accS, accT);
-            OLIVE_STEPS(accS, nS)
-            if (HAS_T) OLIVE_STEPS(accT, nT)
+            if (NORMS && vt % n_p == p) {
+                OLIVE_STEPS(accS, nS, 0, true)
+                OLIVE_STEPS(accT, nT, 1, true)
+            } else {
+                OLIVE_STEPS(accS, nS, 0, false)
+                if (HAS_T) OLIVE_STEPS(accT, nT, 1, false)
+            }
             tile_end(vt, row0);
         }
 #undef OLIVE_STEPS
@@ -443,6 +485,22 @@ struct Kernel {
             }
     }
 
+    // The wavefront's largest squared norms into the call's, as norms with the margin the
+    // rounding bounds use (fp32 sums of d / 2 squares, the dot products' own rounding and
+    // the square root stay far inside 1e-4).
+    static __device__ __forceinline__ void publish_norms(const ScoreArgs &a,
+                                                         const float (&wsq)[2], int lane) {
+#pragma unroll
+        for (int m = 0; m < (HAS_T ? 2 : 1); ++m) {
+            float x = wsq[m];
+            for (int off = 16; off > 0; off >>= 1) x = fmaxf(x, __shfl_xor(x, off));
+            const float n = sqrtf(x) * (1.0001f * (1.0f + 0x1p-10f));
+            // norms are not negative: their bits order as they do
+            if (lane == 0)
+                atomicMax((uint32_t *)const_cast<Sched *>(a.sched)->wmax + m, __float_as_uint(n));
+        }
+    }
+
     static __device__ __forceinline__ void run(ScoreArgs a) {
         const int t_valid = a.sched->t_valid;
         const int64_t n_scored = TOPK ? a.sched->n_scored : 0;
@@ -518,18 +576,20 @@ struct Kernel {
             // Top-K lists only where they are used: the scored rows are compacted first,
             // so only position tiles starting below n_scored hold any.
             const bool lists = TOPK && (int64_t)p * BT < n_scored;
+            float wsq[2] = {0.f, 0.f};
             if (lists) {
-                sweep<true>(a, L, vt0, vt1, nS, nT, accS, accT, [&](int vt, int row0) {
+                sweep<true>(a, L, vt0, vt1, nS, nT, accS, accT, p, n_p, wsq, [&](int vt, int row0) {
                     if (row0 != vt * BV) mask_mma(L, accS, accT, row0, vt * BV);
                     fold<true>(accS, accT, RS, RT, AA, BB, KS, KT, a,
                                row0 + L.wv * 128 + 4 * L.h, vt - vt0);
                 });
             } else {
-                sweep<true>(a, L, vt0, vt1, nS, nT, accS, accT, [&](int vt, int row0) {
+                sweep<true>(a, L, vt0, vt1, nS, nT, accS, accT, p, n_p, wsq, [&](int vt, int row0) {
                     if (row0 != vt * BV) mask_mma(L, accS, accT, row0, vt * BV);
                     fold<false>(accS, accT, RS, RT, AA, BB, KS, KT, a,
                                 row0 + L.wv * 128 + 4 * L.h, vt - vt0);
                 });
+                if (NORMS) publish_norms(a, wsq, L.lane);
             }
 
             // Merge lanes l and l+32 (same columns, interleaved vocabulary rows).
@@ -761,7 +821,8 @@ struct Kernel {
                 w.y = ok[cb] ? pack_bf16x2(gr[2], gr[3]) : 0u;
                 return w;
             };
-            sweep<false>(a, L, vt0, vt1, nS, nT, accS, accT, [&](int vt, int row0) {
+            float wsq[2];
+            sweep<false>(a, L, vt0, vt1, nS, nT, accS, accT, p, n_p, wsq, [&](int vt, int row0) {
                 const int vlo = vt * BV;
                 const int vw0 = row0 + L.wv * 128;   // the wave's first row
                 if (row0 == vlo) {
@@ -892,7 +953,8 @@ struct Kernel {
             const int vt0 = (int)((int64_t)a.n_vtiles * s / ns);
             const int vt1 = (int)((int64_t)a.n_vtiles * (s + 1) / ns);
             floatx16 accS[4][2], accT[4][2];
-            sweep<false>(a, L, vt0, vt1, nS, nT, accS, accT, [&](int vt, int row0) {
+            float wsq[2];
+            sweep<false>(a, L, vt0, vt1, nS, nT, accS, accT, p, n_p, wsq, [&](int vt, int row0) {
                 // rows of a shifted last tile below vt * BV get -2^99 in both models:
                 // p_hi = 0 there, and r stays finite
                 if (row0 != vt * BV) mask_mma(L, accS, accT, row0, vt * BV);
@@ -944,10 +1006,10 @@ struct Kernel {
     }
 };
 
-template <bool HAS_T, bool SAME, bool REV, bool TOPK>
+template <bool HAS_T, bool SAME, bool REV, bool TOPK, bool NORMS = false>
 __global__ void __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1)))
 score_mfma_kernel(ScoreArgs a) {
-    Kernel<HAS_T, SAME, REV, TOPK>::run(a);
+    Kernel<HAS_T, SAME, REV, TOPK, NORMS>::run(a);
 }
 
 template <bool HAS_T>
@@ -978,8 +1040,14 @@ hipError_t launch_score_dz(const ScoreArgs &a, const DzArgs &z, bool has_t, int 
 }
 
 hipError_t launch_score_mfma(const ScoreArgs &a, bool has_t, bool same_scale, bool rev,
-                             bool topk, int grid, hipStream_t st) {
+                             bool topk, bool norms, int grid, hipStream_t st) {
     if (grid <= 0) return hipSuccess;
+    if (norms) {   // a call without a context: KL(teacher || student) at most
+        if (!has_t || rev || topk) return hipErrorInvalidValue;
+        if (same_scale) score_mfma_kernel<true, true, false, false, true><<<grid, 256, 0, st>>>(a);
+        else score_mfma_kernel<true, false, false, false, true><<<grid, 256, 0, st>>>(a);
+        return hipGetLastError();
+    }
 #define OLIVE_SCORE(S_, R_, K_) score_mfma_kernel<true, S_, R_, K_><<<grid, 256, 0, st>>>(a)
     if (has_t) {
         if (same_scale) {

@@ -133,3 +133,34 @@ def test_generic_exact_decision_parts(dtype, ties):
     hip = run_hip(wl, outputs=FORWARD)
     assert hip["stats"]["kernel"] == "generic" and hip["stats"]["flagged"] >= min(ties, 300)
     compare(hip, wl, label="parts-%s-%d" % (dtype, ties))
+
+
+# A call without a context forms its weight norms itself: in the scoring pass (from the
+# units of position tile 0; V = 3001 shifts the last vocabulary tile), or after it for the
+# models with flagged rows (generic kernel). Rows 0 and T - 1 tie exactly.
+@pytest.mark.parametrize("simple", [False, True], ids=["mfma", "generic"])
+@pytest.mark.parametrize("T,V,scales", [(1, 256, (1.0, 1.0)), (130, 3001, (1.0, 1.0)),
+                                        (300, 40000, (2.0, 0.75))])
+def test_static_call_forms_its_own_norms(T, V, scales, simple):
+    say("static norms", T, V, scales, simple)
+    wl = custom("norms", num_seqs=1, seq_len=T, vocab=V, d_student=64, d_teacher=192,
+                cut_rule=("frac", 0.0, 0.0), target_source="uniform")
+    wl["scale_student"], wl["scale_teacher"] = scales
+    wl["w_teacher"][:, V - 1] *= 30.0   # the largest norm in the last row
+    for m in ("student", "teacher"):
+        h, w = wl["h_" + m], wl["w_" + m]
+        for r in (0, T - 1):
+            j = int(torch.argmax(h[r].float() @ w.float()))
+            w[:, (j + V // 3) % V] = w[:, j]
+    vd = [wl["w_" + m].t().contiguous() for m in ("student", "teacher")]
+    o = {k: torch.full((T,), float("nan"), device="cuda") for k in ("kl", "logp_s", "logp_t")}
+    o.update({k: torch.full((T,), -7, dtype=torch.int32, device="cuda") for k in ("am_s", "am_t")})
+    desc = L.make_desc(V, 64, 192, L.OLIVE_BF16, L.OLIVE_W_VD, *scales, max_positions=T, max_seqs=1,
+                       flags=L.OLIVE_FLAG_SIMPLE_KERNEL if simple else 0)
+    batch = L.make_batch(wl["cu_seqlens"], wl["cut"], wl["targets"], wl["h_student"],
+                         wl["h_teacher"], wl["valid_len"])
+    for _ in range(2):
+        L.olive_kl_masked_static(desc, vd[0], vd[1], batch, o["kl"], None, o["logp_s"],
+                                 o["logp_t"], o["am_s"], o["am_t"])
+    torch.cuda.synchronize()
+    compare({k: to_np(v) for k, v in o.items()}, wl, label="static-%d-%d" % (T, V))
