@@ -65,6 +65,43 @@ __device__ __forceinline__ double wave_dot_exact(const uint16_t *h, const uint16
     return acc;
 }
 
+// The same for N vocabulary rows of W at once (their loads overlap; the same sums as one
+// by one).
+template <int N>
+__device__ __forceinline__ void wave_dots_exact(const uint16_t *h, const uint16_t *W,
+                                                const int (&v)[N], int d, int lane,
+                                                double (&out)[N]) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) out[i] = 0.0;
+    for (int k = lane * 8; k < d; k += 512) {
+        const uint4 hq = *(const uint4 *)(h + k);
+        uint4 wq[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) wq[i] = *(const uint4 *)(W + (int64_t)v[i] * d + k);
+#pragma unroll
+        for (int i = 0; i < N; ++i) out[i] = dot8_f64(hq, wq[i], out[i]);
+    }
+    for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+        for (int i = 0; i < N; ++i) out[i] += __shfl_xor(out[i], off);
+}
+
+// Exact logits of the n candidates ci[0 .. n) (LDS) into cx[0 .. n) (LDS), 4 at a time.
+__device__ __forceinline__ void wave_exact_list(const uint16_t *h, const uint16_t *W, int d,
+                                                int lane, const int32_t *ci, int n, double *cx) {
+    for (int c = 0; c < n; c += 4) {
+        int v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            v[i] = __builtin_amdgcn_readfirstlane(ci[c + i < n ? c + i : n - 1]);
+        double x[4];
+        wave_dots_exact<4>(h, W, v, d, lane, x);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (lane == i && c + i < n) cx[c + i] = x[i];
+    }
+}
+
 // |h|^2 in fp32 by one wavefront.
 __device__ __forceinline__ float wave_sumsq(const uint16_t *h, int d, int lane) {
     float acc = 0.f;

@@ -165,8 +165,9 @@ olive_status backward_init(olive_score_ctx *c, hipStream_t st) {
     return ok ? OLIVE_OK : OLIVE_E_HIP;
 }
 
-// Top-K lists need two splits at least (16 listed entries) and at most 1024
-// vocabulary tiles per split (the 16-bit row ordinal of a list key).
+// Top-K lists need two splits at least (16 listed entries; more than one makes the
+// preparation kernel take as many as cost no more) and at most 1024 vocabulary tiles per
+// split (the 16-bit row ordinal of a list key).
 int topk_min_splits(int n_vtiles) {
     const int s = (n_vtiles + 1023) / 1024;
     return s > 2 ? s : 2;
@@ -222,7 +223,9 @@ olive_status run(olive_score_ctx *ctx, const olive_batch *b, const olive_spans *
     const int n_vtiles = (int)((V + vrows - 1) / vrows);
     s = check_hip(launch_prep(*b, spans, region_only, V, ctx->seqbuf, ctx->sched, ctx->err, counts,
                               wide ? WIDE_BT : (mfma ? MFMA_BT : SIMPLE_BT), n_vtiles, grid,
-                              topk ? topk_min_splits(n_vtiles) : 1,
+                              // (every call of a context on the 256 x 128 kernel alike:
+                              // asking for top-K leaves the other outputs as they are)
+                              mfma && !wide && !ctx->no_init ? topk_min_splits(n_vtiles) : 1,
                               ctx->fstride, jsd ? MFMA_BT : 0, kOneChunk, st));
     if (s) return s;
     s = check_hip(launch_rowmap(*b, spans, region_only, V, ctx->seqbuf, ctx->sched, ctx->rowmap,

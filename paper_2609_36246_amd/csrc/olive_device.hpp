@@ -93,27 +93,48 @@ __device__ __forceinline__ void unit_tile_split(int64_t q, int n_p, int ns, int 
 // at V = 151936, d 2048 + 4096: 2.40 ms a call with 32 units on 256 compute units, 0.48 ms
 // with 198, the fewest that give each at most 3 vocabulary tiles).
 // Called by whole wavefronts: lane l tries the counts l + 1, l + 65, ...
+// most: the largest count within 1/32 of the least cost instead. The top-K lists take it:
+// each split keeps 8 entries, and a (row, model) pair whose set may hold more of one
+// split's goes through the vocabulary filter (3124 positions at V = 151936, d 1536 +
+// 3584: 10 splits cost as much as 30, but with 10 the filter and the exact stage took 1.45
+// ms of the call, with 30 0.48 ms).
 __device__ __forceinline__ int pick_splits(int n_p, int n_vtiles, int G, int smin, int smax,
-                                           int tile_rows, int64_t fstride) {
+                                           int tile_rows, int64_t fstride, bool most = false) {
     smax = n_vtiles < smax ? n_vtiles : smax;
     smin = smin < smax ? smin : smax;
-    uint64_t best = ~0ull;
-    for (int s = (int)(threadIdx.x & 63) + 1; s <= smax; s += 64) {
-        if (s < smin) continue;
+    constexpr int PER_LANE = MAX_SPLITS_FEW / 64;
+    uint64_t cost[PER_LANE], best = ~0ull;
+#pragma unroll
+    for (int i = 0; i < PER_LANE; ++i) {
+        const int s = (int)(threadIdx.x & 63) + 1 + 64 * i;
+        cost[i] = ~0ull;
+        if (s < smin || s > smax) continue;
         if (s > MAX_SPLITS &&
             ((int64_t)n_p * s > G || (int64_t)n_p * tile_rows * s > fstride))
             continue;
         // n_p < 2^31 / 128: the units of MAX_SPLITS splits fit 32 bits
         const uint32_t rounds = ((uint32_t)n_p * (uint32_t)s + (uint32_t)G - 1u) / (uint32_t)G;
         const uint32_t per = (uint32_t)(n_vtiles + s - 1) / (uint32_t)s;
-        const uint64_t key = ((uint64_t)rounds * per << 9) | (uint64_t)s;
+        cost[i] = (uint64_t)rounds * per;
+        const uint64_t key = (cost[i] << 9) | (uint64_t)s;
         best = key < best ? key : best;
     }
     for (int off = 32; off > 0; off >>= 1) {
         const uint64_t o = __shfl_xor(best, off);
         best = o < best ? o : best;
     }
-    return __builtin_amdgcn_readfirstlane((int)(best & 511u));
+    int ns = (int)(best & 511u);
+    if (most) {
+        const uint64_t lim = (best >> 9) + (best >> 14);
+#pragma unroll
+        for (int i = 0; i < PER_LANE; ++i)
+            if (cost[i] <= lim) ns = (int)(threadIdx.x & 63) + 1 + 64 * i;
+        for (int off = 32; off > 0; off >>= 1) {
+            const int o = __shfl_xor(ns, off);
+            ns = o > ns ? o : ns;
+        }
+    }
+    return __builtin_amdgcn_readfirstlane(ns);
 }
 
 // The splits of a pass over the scored rows (logit gradient, Jensen-Shannon), or over t_rows

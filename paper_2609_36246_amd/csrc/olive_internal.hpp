@@ -78,6 +78,7 @@ TopkWork topk_carve(void *base, int64_t cap, int32_t *n, int32_t *nfb);
 constexpr int MAX_SPLITS = 32;
 constexpr int MAX_SPLITS_FEW = 256;
 constexpr int SPLIT_WORDS = MAX_SPLITS_FEW / 32;
+constexpr int MAX_SPLITS_TOPK = 64;   // of a call with top-K lists (one lane per split)
 constexpr int kOneChunk = 0x7fffffff;   // a pass that takes the scored rows in one chunk
 
 // Device-side schedule of one call, written by the preparation kernel.

@@ -215,7 +215,8 @@ prep_kernel(const int32_t *__restrict__ cu, const int32_t *__restrict__ cut,
     }
     const int t_valid = carry;   // compacted rows: valid, or in-region when region-only
     const int n_p = (t_valid + tile_rows - 1) / tile_rows;
-    const int ns = pick_splits(n_p, n_vtiles, grid, min_splits, max_splits, tile_rows, fstride);
+    const int ns = pick_splits(n_p, n_vtiles, grid, min_splits, max_splits, tile_rows, fstride,
+                               min_splits > 1);
     if (tid == 0) {
         cvalid[B] = carry;
         cscored[B] = carry_sc;
@@ -413,7 +414,7 @@ hipError_t launch_prep(const olive_batch &b, const olive_spans *spans, bool regi
                                             b.total_positions, b.region, span_args(spans),
                                             region_only ? 1 : 0, seqbuf, sched, err, counts,
                                             tile_rows, n_vtiles, grid, min_splits,
-                                            min_splits > 1 ? MAX_SPLITS : MAX_SPLITS_FEW,
+                                            min_splits > 1 ? MAX_SPLITS_TOPK : MAX_SPLITS_FEW,
                                             fstride, pass_tile, pass_chunk);
     return hipGetLastError();
 }

@@ -32,18 +32,20 @@
 
 namespace olive {
 
-constexpr int TK_CAND = MAX_SPLITS * TK_LIST;   // listed entries of one (row, model)
-// Rank n <= TK_CAND candidates (exact values cx, indices ci in LDS; kTkEmpty marks a
-// skipped slot) and write the 16 best of row j, model m.
+constexpr int TK_CAND = MAX_SPLITS_TOPK * TK_LIST;   // listed entries of one (row, model)
+constexpr int TK_PER_LANE = TK_CAND / 64;
+static_assert(TK_CAP <= TK_CAND, "rank_and_write holds either list");
+// Rank n <= TK_CAND candidates (exact values cx, indices ci in LDS) and write the 16 best
+// of row j, model m.
 __device__ __forceinline__ void rank_and_write(const double *cx, const int *ci, int n, int lane,
                                                int64_t j, int m, float *list_v,
                                                int32_t *list_i) {
-    double kv[4];
-    int ki[4];
+    double kv[TK_PER_LANE];
+    int ki[TK_PER_LANE];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
+    for (int t = 0; t < TK_PER_LANE; ++t) {
         const int c = lane + 64 * t;
-        const bool ok = c < n && cx[c] != kTkEmpty;
+        const bool ok = c < n;
         kv[t] = ok ? cx[c] : kTkEmpty;
         ki[t] = ok ? ci[c] : kTkNoIdx;
     }
@@ -51,14 +53,14 @@ __device__ __forceinline__ void rank_and_write(const double *cx, const int *ci, 
         double bv = kv[0];
         int bi = ki[0], bt = 0;
 #pragma unroll
-        for (int t = 1; t < 4; ++t)
+        for (int t = 1; t < TK_PER_LANE; ++t)
             if (tk_before(kv[t], ki[t], bv, bi)) { bv = kv[t]; bi = ki[t]; bt = t; }
         double wv = bv;
         int wi = bi;
         wave_best(wv, wi);
         if (bv == wv && bi == wi) {             // candidate indices are unique
 #pragma unroll
-            for (int t = 0; t < 4; ++t)
+            for (int t = 0; t < TK_PER_LANE; ++t)
                 if (t == bt) { kv[t] = kTkEmpty; ki[t] = kTkNoIdx; }
         }
         if (lane == 0) {
@@ -68,12 +70,13 @@ __device__ __forceinline__ void rank_and_write(const double *cx, const int *ci, 
     }
 }
 
-// One wavefront per compacted in-region row, for each model in turn.
+// One wavefront per compacted in-region row and model (blockIdx.y).
 __global__ void __launch_bounds__(256)
 topk_select_kernel(ScoreArgs a, TopkWork w) {
     __shared__ float cv[4][TK_CAND];
     __shared__ int ci[4][TK_CAND];
     __shared__ double cx[4][TK_CAND];
+    __shared__ int cs[4][TK_CAND];
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const int64_t j = (int64_t)blockIdx.x * 4 + wid;
     Sched *sched = const_cast<Sched *>(a.sched);
@@ -84,75 +87,77 @@ topk_select_kernel(ScoreArgs a, TopkWork w) {
     const int ns = sched->n_splits;
     const int nc = ns * TK_LIST;
     const int64_t fs = a.fstride, ps = sched->pstride;
-    for (int m = 0; m < 2; ++m) {
-        const int d = m ? a.dt : a.ds;
-        const uint16_t *h = (const uint16_t *)(m ? a.ht : a.hs) + g * d;
-        const uint16_t *W = (const uint16_t *)(m ? a.wt : a.ws);
-        const float hh = wave_sumsq(h, d, lane);
-        if (hh == 0.f) {   // h = 0: every exact logit is 0, the set is 0..15
-            if (lane < TOPK_K) {
-                w.list_v[(j * 2 + m) * TOPK_K + lane] = 0.f;
-                w.list_i[(j * 2 + m) * TOPK_K + lane] = lane;
-            }
-            continue;
+    const int m = blockIdx.y;
+    const int d = m ? a.dt : a.ds;
+    const uint16_t *h = (const uint16_t *)(m ? a.ht : a.hs) + g * d;
+    const uint16_t *W = (const uint16_t *)(m ? a.wt : a.ws);
+    const float hh = wave_sumsq(h, d, lane);
+    if (hh == 0.f) {   // h = 0: every exact logit is 0, the set is 0..15
+        if (lane < TOPK_K) {
+            w.list_v[(j * 2 + m) * TOPK_K + lane] = 0.f;
+            w.list_i[(j * 2 + m) * TOPK_K + lane] = lane;
         }
-        float fl = -__builtin_inff();
-        if (lane < ns) {
-            for (int e = 0; e < TK_LIST; ++e) {
-                cv[wid][lane * TK_LIST + e] =
-                    a.part[(F_TK + m * TK_FIELDS + e) * fs + lane * ps + j];
-                ci[wid][lane * TK_LIST + e] = __float_as_int(
-                    a.part[(F_TK + m * TK_FIELDS + TK_LIST + e) * fs + lane * ps + j]);
-            }
-            fl = a.part[(F_TK + m * TK_FIELDS + 2 * TK_LIST) * fs + lane * ps + j];
-        }
-        __builtin_amdgcn_wave_barrier();
-        // z16: the 16th largest listed value (lane l < ns walks split l's sorted list)
-        int ptr = 0;
-        double z16 = kTkEmpty;
-        for (int r = 0; r < TOPK_K; ++r) {
-            double hv = kTkEmpty;
-            int hi = kTkNoIdx;
-            if (lane < ns && ptr < TK_LIST) {
-                hv = cv[wid][lane * TK_LIST + ptr];
-                hi = ci[wid][lane * TK_LIST + ptr];
-            }
-            double bv = hv;
-            int bi = hi;
-            wave_best(bv, bi);
-            if (lane < ns && ptr < TK_LIST && hv == bv && hi == bi) ++ptr;
-            z16 = bv;
-        }
-        const float delta = (float)d * 0x1p-23f * (sqrtf(hh) * (1.0f + 0x1p-10f)) *
-                            (a.wmax_dev ? a.wmax_dev[m] : (m ? a.wmax_t : a.wmax_s));
-        const float thr = (float)z16 - 2.f * delta;
-        // every logit that can reach the exact top-16 is listed unless a floor reaches
-        // thr (a floor or threshold that is not finite queues the pair as well)
-        if (__any(lane < ns && !(fl < thr))) {
-            if (lane == 0) {
-                const FilterQueue &f = w.fq;
-                const int q = atomicAdd(&f.n[m], 1);
-                if (q < f.cap) {
-                    f.qj[m * f.cap + q] = (int32_t)j;
-                    f.qthr[m * f.cap + q] = thr;
-                    f.qcnt[m * f.cap + q] = 0;
-                }
-            }
-            continue;
-        }
-        // exact values of the listed entries whose bucket reaches thr (an empty slot,
-        // index outside [0, V), never does)
-        for (int c = 0; c < nc; ++c) {
-            double x = kTkEmpty;
-            const int v = ci[wid][c];
-            if (bucket_ub(cv[wid][c]) >= thr && (unsigned)v < (unsigned)a.V)
-                x = wave_dot_exact(h, W + (int64_t)v * d, d, lane);
-            if (lane == 0) cx[wid][c] = x;
-        }
-        __builtin_amdgcn_wave_barrier();
-        rank_and_write(cx[wid], ci[wid], nc, lane, j, m, w.list_v, w.list_i);
-        __builtin_amdgcn_wave_barrier();
+        return;
     }
+    float fl = -__builtin_inff();
+    if (lane < ns) {
+        for (int e = 0; e < TK_LIST; ++e) {
+            cv[wid][lane * TK_LIST + e] =
+                a.part[(F_TK + m * TK_FIELDS + e) * fs + lane * ps + j];
+            ci[wid][lane * TK_LIST + e] = __float_as_int(
+                a.part[(F_TK + m * TK_FIELDS + TK_LIST + e) * fs + lane * ps + j]);
+        }
+        fl = a.part[(F_TK + m * TK_FIELDS + 2 * TK_LIST) * fs + lane * ps + j];
+    }
+    __builtin_amdgcn_wave_barrier();
+    // z16: the 16th largest listed value (lane l < ns walks split l's sorted list)
+    int ptr = 0;
+    double z16 = kTkEmpty;
+    for (int r = 0; r < TOPK_K; ++r) {
+        double hv = kTkEmpty;
+        int hi = kTkNoIdx;
+        if (lane < ns && ptr < TK_LIST) {
+            hv = cv[wid][lane * TK_LIST + ptr];
+            hi = ci[wid][lane * TK_LIST + ptr];
+        }
+        double bv = hv;
+        int bi = hi;
+        wave_best(bv, bi);
+        if (lane < ns && ptr < TK_LIST && hv == bv && hi == bi) ++ptr;
+        z16 = bv;
+    }
+    const float delta = (float)d * 0x1p-23f * (sqrtf(hh) * (1.0f + 0x1p-10f)) *
+                        (a.wmax_dev ? a.wmax_dev[m] : (m ? a.wmax_t : a.wmax_s));
+    const float thr = (float)z16 - 2.f * delta;
+    // every logit that can reach the exact top-16 is listed unless a floor reaches
+    // thr (a floor or threshold that is not finite queues the pair as well)
+    if (__any(lane < ns && !(fl < thr))) {
+        if (lane == 0) {
+            const FilterQueue &f = w.fq;
+            const int q = atomicAdd(&f.n[m], 1);
+            if (q < f.cap) {
+                f.qj[m * f.cap + q] = (int32_t)j;
+                f.qthr[m * f.cap + q] = thr;
+                f.qcnt[m * f.cap + q] = 0;
+            }
+        }
+        return;
+    }
+    // exact values of the listed entries whose bucket reaches thr (an empty slot,
+    // index outside [0, V), never does)
+    int n = 0;
+    for (int c0 = 0; c0 < nc; c0 += 64) {
+        const int c = c0 + lane;
+        const int v = c < nc ? ci[wid][c] : -1;
+        const bool in = c < nc && bucket_ub(cv[wid][c]) >= thr && (unsigned)v < (unsigned)a.V;
+        const uint64_t mask = __ballot(in);
+        if (in) cs[wid][n + __popcll(mask & ((1ull << lane) - 1ull))] = v;
+        n += __popcll(mask);
+    }
+    __builtin_amdgcn_wave_barrier();
+    wave_exact_list(h, W, d, lane, cs[wid], n, cx[wid]);
+    __builtin_amdgcn_wave_barrier();
+    rank_and_write(cx[wid], cs[wid], n, lane, j, m, w.list_v, w.list_i);
 }
 
 // One wavefront per queued pair: exact values of its kept indices, ranked. A pair
@@ -183,11 +188,9 @@ topk_exact_kernel(ScoreArgs a, TopkWork w) {
         const uint16_t *h = (const uint16_t *)(m ? a.ht : a.hs) + g * d;
         const uint16_t *W = (const uint16_t *)(m ? a.wt : a.ws);
         const int32_t *cd = f.cand + ((int64_t)m * f.cap + q) * f.ccap;
-        for (int c = 0; c < n; ++c) {
-            const int v = cd[c];
-            const double x = wave_dot_exact(h, W + (int64_t)v * d, d, lane);
-            if (lane == 0) { cx[wid][c] = x; ci[wid][c] = v; }
-        }
+        for (int c = lane; c < n; c += 64) ci[wid][c] = cd[c];
+        __builtin_amdgcn_wave_barrier();
+        wave_exact_list(h, W, d, lane, ci[wid], n, cx[wid]);
         __builtin_amdgcn_wave_barrier();
         rank_and_write(cx[wid], ci[wid], n, lane, j, m, w.list_v, w.list_i);
         __builtin_amdgcn_wave_barrier();
@@ -306,7 +309,7 @@ hipError_t launch_topk(const ScoreArgs &a, const TopkWork &w, const TopkOut &out
                        int64_t max_rows, hipStream_t st) {
     if (max_rows <= 0) return hipSuccess;
     const dim3 rows((unsigned)((max_rows + 3) / 4));
-    topk_select_kernel<<<rows, 256, 0, st>>>(a, w);
+    topk_select_kernel<<<dim3(rows.x, 2), 256, 0, st>>>(a, w);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     e = launch_filter(a, w.fq, st);
