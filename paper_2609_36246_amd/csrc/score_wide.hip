@@ -79,6 +79,16 @@ __device__ __forceinline__ void stat_put(int m, int cb, const Run &R) {
     p[12 * 256] = __int_as_float(R.idx);
 }
 
+// The difference sums of a column block between the folds, in LDS for the same reason:
+// [sum][cb][thread], 12 KB. Sums: the first model's fp16 weights, its weighted logits,
+// and the same weights times the second model's logits.
+enum { ACC_ZH = 0, ACC_A1 = 1, ACC_A2 = 2 };
+__shared__ float x_acc[3 * 4 * 256];
+
+__device__ __forceinline__ float &acc_at(int k, int cb) {
+    return x_acc[(k * 4 + cb) * 256 + threadIdx.x];
+}
+
 typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
 
 // x, y to a packed fp16 pair (x low), rounded to nearest even (one v_cvt_pk_f16_f32).
@@ -229,8 +239,8 @@ struct Wide {
     struct Cursor {
         const char *w, *h;       // W and H tile of the step to prefetch
         int64_t wstep, hstep;    // bytes from one panel to the next (0 past the unit's end)
-        int m, kk, cnt, vt;      // model block (1 = teacher), step in the block, its length
-        int vt1, nS, nT, p;
+        int m, vt;               // model block (1 = teacher), vocabulary tile
+        int vt1, p;
     };
     using Args = ScoreArgs;
     using Pipe = WidePipe<Wide>;
@@ -238,8 +248,6 @@ struct Wide {
     template <int M>
     static __device__ __forceinline__ void enter(Cursor &C, const ScoreArgs &a, int vt) {
         C.m = M;
-        C.kk = 0;
-        C.cnt = M ? C.nT : C.nS;
         C.vt = vt;
         C.w = (const char *)(M ? a.wpt : a.wps) + (int64_t)vt * XV * XROW;
         C.h = (const char *)(M ? a.hpt : a.hps) + (int64_t)C.p * XT * XROW;
@@ -250,25 +258,16 @@ struct Wide {
     // The first model's block of a tile, then the second's, then the next tile's first;
     // past the unit's last block the prefetches repeat its last step.
     static __device__ __forceinline__ void turn(Cursor &C, const ScoreArgs &a) {
-        if (C.kk == C.cnt) {
-            if (HAS_T && C.m == M1) {
-                enter<M2>(C, a, C.vt);
-            } else if (C.vt + 1 < C.vt1) {
-                enter<M1>(C, a, C.vt + 1);
-            } else {
-                C.w -= C.wstep;
-                C.h -= C.hstep;
-                C.wstep = 0;
-                C.hstep = 0;
-                C.cnt = 0x7fffffff;
-            }
+        if (HAS_T && C.m == M1) {
+            enter<M2>(C, a, C.vt);
+        } else if (C.vt + 1 < C.vt1) {
+            enter<M1>(C, a, C.vt + 1);
+        } else {
+            C.w -= C.wstep;
+            C.h -= C.hstep;
+            C.wstep = 0;
+            C.hstep = 0;
         }
-    }
-
-    static __device__ __forceinline__ void advance(Cursor &C) {
-        C.w += C.wstep;
-        C.h += C.hstep;
-        C.kk += 1;
     }
 
     // Add kMasked to the rows at or past V of the padded last tile (one MFMA per block:
@@ -302,30 +301,6 @@ struct Wide {
             for (int r = 0; r < 4; ++r) z[4 * j + r] = agpr_read(acc[4 * q + j][cb][r]);
     }
 
-    // One model block of COUNT_ K steps into acc: the first step has no pending half, the
-    // block's last half runs after the loop.
-#define OLIVE_XSTEPS(COUNT_)                                                              \
-            {                                                                             \
-                XFragA PA;                                                                \
-                XFragB PB;                                                                \
-                Pipe::template step<0>(a, L, C, st, acc, PA, PB);                         \
-                st = st + 1 == XNST ? 0 : st + 1;                                         \
-                if ((COUNT_) > 1) {                                                       \
-                    Pipe::template step<1>(a, L, C, st, acc, PA, PB);                     \
-                    st = st + 1 == XNST ? 0 : st + 1;                                     \
-                    for (int k = 2; k < (COUNT_); ++k) {                                  \
-                        Pipe::template step<2>(a, L, C, st, acc, PA, PB);                 \
-                        st = st + 1 == XNST ? 0 : st + 1;                                 \
-                    }                                                                     \
-                    Pipe::template mma_half<1, false, 0, 0>(PA, PB, acc, C, L, 0u, x_ring,   \
-                                                           PA, PB);               \
-                } else {                                                                  \
-                    Pipe::template mma_half<1, true, 0, 0>(PA, PB, acc, C, L, 0u, x_ring,    \
-                                                          PA, PB);                \
-                }                                                                         \
-                __builtin_amdgcn_sched_barrier(0);                                        \
-            }
-
     static __device__ __forceinline__ void run(ScoreArgs a) {
         const int t_valid = a.sched->t_valid;
         const int n_p = a.sched->n_ptiles;
@@ -344,30 +319,24 @@ struct Wide {
             const int vt0 = (int)((int64_t)a.n_vtiles * s / ns);
             const int vt1 = (int)((int64_t)a.n_vtiles * (s + 1) / ns);
 
-            // per column: the first model's fp16 weight sum, its weighted logit sum, and
-            // the same weights times the second model's logits
-            float ZH[4], A1[4], A2[4];
 #pragma unroll
             for (int cb = 0; cb < 4; ++cb) {
                 stat_put(0, cb, Run{kNegInf, kNegInf, 0.f, 0x7fffffff});
                 stat_put(1, cb, Run{kNegInf, kNegInf, 0.f, 0x7fffffff});
-                ZH[cb] = 0.f;
-                A1[cb] = 0.f;
-                A2[cb] = 0.f;
+                if (HAS_T) {
+                    acc_at(ACC_ZH, cb) = 0.f;
+                    acc_at(ACC_A1, cb) = 0.f;
+                    acc_at(ACC_A2, cb) = 0.f;
+                }
             }
             uint32_t eh[4][4][8];   // [row-block quarter][cb][pair]
             floatx4 acc[16][4];
 
             Cursor C;
             C.vt1 = vt1;
-            C.nS = nS;
-            C.nT = nT;
             C.p = p;
             enter<M1>(C, a, vt0);
-#pragma unroll
-            for (int i = 0; i < XNST - 1; ++i) Pipe::issue(a, L, C, i);
-            __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): no scalar load pending
-            int st = 0;
+            typename Pipe::Ring ring = Pipe::prologue(L, C);
             // the first two tiles of a unit only measure the period (it straddles the
             // unit change)
             PhaseClock PH{0u, 0u};
@@ -377,7 +346,7 @@ struct Wide {
                 const int vbase = row0 + 4 * L.g;
                 if (lock && L.wid == 0) phase_lock<XDMA_STEP * (XNST - 2)>(PH, G);
                 if constexpr (HAS_T) {
-                OLIVE_XSTEPS(M1 ? nT : nS)
+                Pipe::block(a, L, C, ring, M1 ? nT : nS, acc);
                 if (row0 + XV > a.V) mask_tail(L, acc, row0, a.V);
                 {
                     const float inf = opaque_inf(), one = opaque_one();
@@ -394,8 +363,9 @@ struct Wide {
                         }
                         // one rescale per column and tile, to the tile's max
                         const float resc = fast_exp2((m0 - R.best) * c1);
-                        float zsum = R.z * resc, hsum = ZH[cb] * resc, asum = A1[cb] * resc;
-                        A2[cb] *= resc;
+                        float zsum = R.z * resc, hsum = acc_at(ACC_ZH, cb) * resc,
+                              asum = acc_at(ACC_A1, cb) * resc;
+                        acc_at(ACC_A2, cb) *= resc;
                         const float mneg = fmaf(-R.best, c1, 15.0f);
 #pragma unroll
                         for (int qq = 0; qq < 4; ++qq) {
@@ -405,33 +375,31 @@ struct Wide {
                             first_weights(z, c1, mneg, one, zsum, hsum, asum, eh[qq][cb]);
                         }
                         R.z = zsum;
-                        ZH[cb] = hsum;
-                        A1[cb] = asum;
-                        // Pin the weighted sums here: otherwise the compiler sinks them
-                        // past the second sweep, keeping the first model's logits alive
-                        // (and spilled) across it.
-                        asm volatile("" : "+v"(ZH[cb]), "+v"(A1[cb]), "+v"(A2[cb]));
+                        acc_at(ACC_ZH, cb) = hsum;
+                        acc_at(ACC_A1, cb) = asum;
                         stat_put(M1, cb, R);
                     }
                 }
                 }
-                OLIVE_XSTEPS(M2 ? nT : nS)
+                Pipe::block(a, L, C, ring, M2 ? nT : nS, acc);
                 if (row0 + XV > a.V) mask_tail(L, acc, row0, a.V);
                 {
                     const float inf = opaque_inf();
 #pragma unroll
                     for (int cb = 0; cb < 4; ++cb) {
                         Run R = stat_get(M2, cb);
+                        float a2 = HAS_T ? acc_at(ACC_A2, cb) : 0.f;
 #pragma unroll
                         for (int qq = 0; qq < 4; ++qq) {
                             __builtin_amdgcn_sched_barrier(0);
                             float z[16];
                             col16(acc, qq, cb, z);
                             if constexpr (HAS_T)
-                                fold_second(z, R, A2[cb], eh[qq][cb], c2, vbase + qq * 64, inf);
+                                fold_second(z, R, a2, eh[qq][cb], c2, vbase + qq * 64, inf);
                             else
                                 fold_student_only(z, R, a.cS, vbase + qq * 64, inf);
                         }
+                        if (HAS_T) acc_at(ACC_A2, cb) = a2;
                         stat_put(M2, cb, R);
                     }
                 }
@@ -444,8 +412,12 @@ struct Wide {
 #pragma unroll
             for (int cb = 0; cb < 4; ++cb) {
                 const float s1 = M1 ? a.sT : a.sS, s2 = M1 ? a.sS : a.sT;
-                float aa = SAME ? A1[cb] - A2[cb] : s1 * A1[cb] - s2 * A2[cb];
-                float zh = ZH[cb];
+                float aa = 0.f, zh = 0.f;
+                if (HAS_T) {
+                    const float a1 = acc_at(ACC_A1, cb), a2 = acc_at(ACC_A2, cb);
+                    aa = SAME ? a1 - a2 : s1 * a1 - s2 * a2;
+                    zh = acc_at(ACC_ZH, cb);
+                }
                 Run R1 = stat_get(M1, cb), R2 = stat_get(M2, cb);
 #pragma unroll
                 for (int off = 16; off <= 32; off <<= 1) {
@@ -502,7 +474,7 @@ struct Wide {
         const int ns = pass_splits(a.sched, t_rows, z.chunk);
         const int64_t n_units = (int64_t)n_p * ns;
         const XLane L = make_lane();
-        const int nS = a.ds / XK, nT = 0;
+        const int nS = a.ds / XK;
         const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
         const int my = (G & 7) == 0 ? xcd * (G >> 3) + slot : (int)blockIdx.x;
         const bool lock = phase_lock_on(G, nS);
@@ -528,19 +500,14 @@ struct Wide {
             floatx4 acc[16][4];
             Cursor C;
             C.vt1 = vt1;
-            C.nS = nS;
-            C.nT = nT;
             C.p = p;
             enter<0>(C, a, vt0);
-#pragma unroll
-            for (int i = 0; i < XNST - 1; ++i) Pipe::issue(a, L, C, i);
-            __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): no scalar load pending
-            int st = 0;
+            typename Pipe::Ring ring = Pipe::prologue(L, C);
             PhaseClock PH{0u, 0u};
             for (int vt = vt0; vt < vt1; ++vt) {
                 const int row0 = vt * XV;
                 if (lock && L.wid == 0) phase_lock<XDMA_STEP * (XNST - 2)>(PH, G);
-                OLIVE_XSTEPS(nS)
+                Pipe::block(a, L, C, ring, nS, acc);
                 // Rows at or past V are not stored (dz_t's rows V .. vp-1 stay zero).
                 // Lane (l16, g) holds rows 16 vb + 4 g .. +3 of column cb: 8 bytes of one
                 // panel row.
@@ -597,7 +564,7 @@ struct Wide {
         const int ns = pass_splits(a.sched, t_rows, z.chunk);
         const int64_t n_units = (int64_t)n_p * ns;
         const XLane L = make_lane();
-        const int nS = a.ds / XK, nT = 0;
+        const int nS = a.ds / XK;
         const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
         const int my = (G & 7) == 0 ? xcd * (G >> 3) + slot : (int)blockIdx.x;
         const bool lock = phase_lock_on(G, nS);
@@ -622,19 +589,14 @@ struct Wide {
             floatx4 acc[16][4];
             Cursor C;
             C.vt1 = vt1;
-            C.nS = nS;
-            C.nT = nT;
             C.p = p;
             enter<0>(C, a, vt0);
-#pragma unroll
-            for (int i = 0; i < XNST - 1; ++i) Pipe::issue(a, L, C, i);
-            __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): no scalar load pending
-            int st = 0;
+            typename Pipe::Ring ring = Pipe::prologue(L, C);
             PhaseClock PH{0u, 0u};
             for (int vt = vt0; vt < vt1; ++vt) {
                 const int row0 = vt * XV;
                 if (lock && L.wid == 0) phase_lock<XDMA_STEP * (XNST - 2)>(PH, G);
-                OLIVE_XSTEPS(nS)
+                Pipe::block(a, L, C, ring, nS, acc);
                 if (row0 + XV > a.V) mask_tail(L, acc, row0, a.V);
                 // the column's max over the tile: the lane's 64 rows, then its 4 row groups
 #pragma unroll
@@ -706,7 +668,6 @@ struct Wide {
             __syncthreads();
         }
     }
-#undef OLIVE_XSTEPS
 };
 
 template <bool SAME, bool HAS_T, bool REV>
@@ -766,10 +727,10 @@ panel_h_kernel(const uint16_t *__restrict__ h, int d, const uint32_t *__restrict
 hipError_t launch_score_wide(const ScoreArgs &a, bool same_scale, bool has_t, bool rev,
                              int grid, hipStream_t st) {
     if (grid <= 0) return hipSuccess;
-    if (a.ds <= 0 || a.ds % XK != 0 || a.vpad % XV != 0 || a.prow % XT != 0 || !a.wps ||
+    if (a.ds <= 0 || a.ds % (2 * XK) != 0 || a.vpad % XV != 0 || a.prow % XT != 0 || !a.wps ||
         !a.hps)
         return hipErrorInvalidValue;
-    if (has_t && (a.dt <= 0 || a.dt % XK != 0 || !a.wpt || !a.hpt)) return hipErrorInvalidValue;
+    if (has_t && (a.dt <= 0 || a.dt % (2 * XK) != 0 || !a.wpt || !a.hpt)) return hipErrorInvalidValue;
     if (rev && !has_t) return hipErrorInvalidValue;
     if (!has_t)
         score_wide_kernel<false, false, false><<<grid, 256, 0, st>>>(a);
@@ -786,7 +747,7 @@ hipError_t launch_score_wide(const ScoreArgs &a, bool same_scale, bool has_t, bo
 
 hipError_t launch_score_wide_dz(const ScoreArgs &a, const DzArgs &z, int grid, hipStream_t st) {
     if (grid <= 0) return hipSuccess;
-    if (a.ds <= 0 || a.ds % XK != 0 || a.vpad % XV != 0 || !a.wps || !a.hps || !z.dz_t ||
+    if (a.ds <= 0 || a.ds % (2 * XK) != 0 || a.vpad % XV != 0 || !a.wps || !a.hps || !z.dz_t ||
         z.c0 % XT != 0 || z.chunk <= 0)
         return hipErrorInvalidValue;
     score_wide_dz_kernel<<<grid, 256, 0, st>>>(a, z);
@@ -796,7 +757,7 @@ hipError_t launch_score_wide_dz(const ScoreArgs &a, const DzArgs &z, int grid, h
 hipError_t launch_score_wide_dz_online(const ScoreArgs &a, const DzArgs &z, int grid,
                                        hipStream_t st) {
     if (grid <= 0) return hipSuccess;
-    if (a.ds <= 0 || a.ds % XK != 0 || a.vpad % XV != 0 || !a.wps || !a.hps || !z.dz_t ||
+    if (a.ds <= 0 || a.ds % (2 * XK) != 0 || a.vpad % XV != 0 || !a.wps || !a.hps || !z.dz_t ||
         !z.mref || !a.part || z.c0 % XT != 0 || z.chunk <= 0)
         return hipErrorInvalidValue;
     score_wide_dz_online_kernel<<<grid, 256, 0, st>>>(a, z);

@@ -6,15 +6,25 @@
 // through global_load_lds_dwordx4, issued two steps ahead; the 16-byte chunk c of stage
 // row r sits in slot c ^ ((r >> 1) & 3), the one XOR swizzle on 16-byte slots measured
 // on gfx950 to keep the 16-row x 4-chunk operand reads free of bank conflicts. The DMA
-// lanes' source offsets (XLane::voff) place the swizzle: from panels written
+// lanes' source offset (XLane::voff) places the swizzle: from panels written
 // pre-swizzled they are linear.
 //
 // A step's 64 MFMAs run in two halves of 8 A row blocks; the previous step's second half
 // runs while this step's first operands are read, one read after each MFMA.
 //
-// The kernel supplies a policy P with its cursor type P::Cursor (fields w and h: the A
-// and B tile of the step to prefetch), P::Args, and P::turn(C, a) (called before a
-// step's prefetch is issued) and P::advance(C) (after).
+// An MFMA holds the matrix pipe for 16 cycles and the wavefront's issue for 4, so up to
+// three other instructions behind each are free, and what stands between a step's last
+// MFMA and the next step's first is not: the cursor and ring arithmetic is therefore placed
+// behind MFMAs late in the step, the B fragments of consecutive steps take turns in two
+// register sets (steps run in pairs: widths are multiples of 64) instead of being copied,
+// and the cursor turns to the next block at a fixed step instead of being tested in each.
+// With the copies, tests and arithmetic at the step's end the calls of the scoring kernel
+// took 5 to 7 % longer (23048 positions at V = 151936, d 2048 + 4096: 34.75 against 33.00
+// ms; 8192 at 1536 + 3584: 10.00 against 9.42).
+//
+// The kernel supplies a policy P with its cursor type P::Cursor (fields w and h: the A and
+// B tile of the step to prefetch; wstep and hstep: bytes to the next step's), P::Args, and
+// P::turn(C, a), which points the cursor at the next block once a block is issued.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -44,17 +54,18 @@ __device__ __forceinline__ uint32_t xring_addr() {
 }
 
 // One global -> LDS DMA of 16 bytes per lane: lane i's bytes land at the wave-uniform
-// LDS address la + OFFL + 16 i; the source is the wave-uniform base plus the lane's
-// 32-bit offset. The instruction's own offset field stays 0 (it would move the LDS
-// address as well).
-template <int OFFL>
+// LDS address la + OFFL + OFF + 16 i; the source is the wave-uniform base plus the lane's
+// 32-bit offset plus OFF. OFF is the instruction's own offset field, which moves both
+// addresses: the 4 DMAs of an operand's step, 1 KB apart on both sides, share one lane
+// offset.
+template <int OFFL, int OFF>
 __device__ __forceinline__ void xdma(const char *base, uint32_t voff, uint32_t la) {
     la = __builtin_amdgcn_readfirstlane(la);
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
-    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%4"
                  :
-                 : "s"(la), "v"(voff), "s"(base), "i"(OFFL)
+                 : "s"(la), "v"(voff), "s"(base), "i"(OFFL), "i"(OFF)
                  : "memory", "m0", "scc");
 #pragma clang diagnostic pop
 }
@@ -64,8 +75,8 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 struct XLane {
     int lane, wid, l16, g;   // g = lane / 16: the lane's 4-row group of an output block
                              // and its 8-element K chunk of an operand fragment
-    uint32_t voff[XDMA];     // per DMA i of an operand: the lane's byte offset within a
-                             // 16 KB tile step (wave part and i * 1 KB included)
+    uint32_t voff;           // DMA 0 of an operand: the lane's byte offset within a 16 KB
+                             // tile step (wave part included; DMA i adds i * 1 KB)
     uint32_t lds_a;          // operand read offset within a stage: W row l16 of block 0
     uint32_t lds_b;          // H row (position) 64 wid + l16 of block 0
 };
@@ -88,9 +99,7 @@ __device__ __forceinline__ XLane make_lane() {
     // DMA lane: 16 bytes at 16 lane of a 1 KB piece of the step's tile. The panels
     // hold every row's 16-byte chunks already in their swizzled slots (panel_w,
     // panel_h), so the copy is linear and lands swizzled.
-#pragma unroll
-    for (int i = 0; i < XDMA; ++i)
-        L.voff[i] = (uint32_t)(L.wid * XDMA * 1024 + i * 1024 + L.lane * 16);
+    L.voff = (uint32_t)(L.wid * XDMA * 1024 + L.lane * 16);
     // operand fragment of a 16-row block: row l16, K chunk g, in slot g ^ ((l16 >> 1) & 3)
     const uint32_t lane_part = (uint32_t)(L.l16 * XROW + ((L.g ^ ((L.l16 >> 1) & 3)) << 4));
     L.lds_a = lane_part;
@@ -108,9 +117,9 @@ struct WidePipe {
     template <int Q>
     static __device__ __forceinline__ void dma_q(const Cursor &C, const XLane &L, uint32_t lw) {
         if constexpr (Q < XDMA)
-            xdma<Q * 1024>(C.w, L.voff[Q], lw);
+            xdma<0, Q * 1024>(C.w, L.voff, lw);
         else
-            xdma<XW_BYTES + (Q - XDMA) * 1024>(C.h, L.voff[Q - XDMA], lw);
+            xdma<XW_BYTES, (Q - XDMA) * 1024>(C.h, L.voff, lw);
     }
 
     template <int QB, int QE>
@@ -121,27 +130,38 @@ struct WidePipe {
         }
     }
 
-    static __device__ __forceinline__ uint32_t stage_w(const XLane &L, int st) {
-        return xring_addr() + (uint32_t)st * XSTAGE + (uint32_t)L.wid * (XDMA * 1024u);
+    // The wavefront's part of the stage at ring offset `off`.
+    static __device__ __forceinline__ uint32_t stage_w(const XLane &L, uint32_t off) {
+        return xring_addr() + off + (uint32_t)L.wid * (XDMA * 1024u);
     }
 
-    static __device__ __forceinline__ void issue(const Args &a, const XLane &L, Cursor &C,
-                                                 int st) {
-        P::turn(C, a);
-        dmas<0, XDMA_STEP>(C, L, stage_w(L, st));
-        P::advance(C);
+    static __device__ __forceinline__ void issue(const XLane &L, Cursor &C, uint32_t off) {
+        dmas<0, XDMA_STEP>(C, L, stage_w(L, off));
+        C.w += C.wstep;
+        C.h += C.hstep;
+    }
+
+    // Ring offsets of the stage of the current step, and of the stage the step refills
+    // (the previous step's).
+    struct Ring {
+        uint32_t rd, wr;
+    };
+    // Before a unit's first step: steps 0 and 1 in flight into stages 0 and 1.
+    static __device__ __forceinline__ Ring prologue(const XLane &L, Cursor &C) {
+#pragma unroll
+        for (int i = 0; i < XNST - 1; ++i) issue(L, C, i * XSTAGE);
+        __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): no scalar load pending
+        return Ring{0u, (XNST - 1) * XSTAGE};
     }
 
     // Half H of a step's A blocks (row blocks 8H .. 8H+7), and the step's B blocks.
     template <int H>
-    static __device__ __forceinline__ void read_a(const XLane &L, int st, XFragA &F) {
-        const char *stage = x_ring + st * XSTAGE;
+    static __device__ __forceinline__ void read_a(const XLane &L, const char *stage, XFragA &F) {
 #pragma unroll
         for (int i = 0; i < 8; ++i)
             F.A[i] = *(const bf16x8 *)(stage + L.lds_a + (8 * H + i) * 1024);
     }
-    static __device__ __forceinline__ void read_b(const XLane &L, int st, XFragB &F) {
-        const char *stage = x_ring + st * XSTAGE;
+    static __device__ __forceinline__ void read_b(const XLane &L, const char *stage, XFragB &F) {
 #pragma unroll
         for (int cb = 0; cb < 4; ++cb)
             F.B[cb] = *(const bf16x8 *)(stage + L.lds_b + cb * 1024);
@@ -164,10 +184,11 @@ struct WidePipe {
 
     // MFMA J (0..31) of half H of a step, then its share of the refill's DMAs Q0 ..
     // Q0+NQ-1 (spread evenly over the 32) and of the interleaved reads, then MFMA J+1.
-    // ZERO: onto zero accumulators (the block's first K step).
-    template <int H, bool ZERO, int Q0, int NQ, int RD, int J>
+    // ZERO: onto zero accumulators (the block's first K step). ADV: after the half's last
+    // DMA, move the cursor's A tile (bit 0), its B tile (bit 1) and the ring (bit 2) on.
+    template <int H, bool ZERO, int Q0, int NQ, int RD, int ADV, int J>
     static __device__ __forceinline__ void mma_from(const XFragA &FA, const XFragB &FB,
-                                                    floatx4 (&acc)[16][4], const Cursor &C,
+                                                    floatx4 (&acc)[16][4], Cursor &C, Ring &R,
                                                     const XLane &L, uint32_t lw,
                                                     const char *stage, XFragA &RA, XFragB &RB) {
         if constexpr (J < 32) {
@@ -179,15 +200,23 @@ struct WidePipe {
             read_at<RD, J>(L, stage, RA, RB);
             __builtin_amdgcn_sched_barrier(0);
             dmas<Q0 + (J * NQ + 31) / 32, Q0 + (J * NQ + NQ + 31) / 32>(C, L, lw);
-            mma_from<H, ZERO, Q0, NQ, RD, J + 1>(FA, FB, acc, C, L, lw, stage, RA, RB);
+            if constexpr ((ADV & 1) && J == 29) C.w += C.wstep;
+            if constexpr ((ADV & 2) && J == 30) C.h += C.hstep;
+            if constexpr ((ADV & 4) && J == 28) {
+                R.wr = R.rd;
+                R.rd = R.rd == (XNST - 1) * XSTAGE ? 0u : R.rd + XSTAGE;
+                // (kept here: the values are not formed again at their uses)
+                asm volatile("" : "+s"(R.rd), "+s"(R.wr));
+            }
+            mma_from<H, ZERO, Q0, NQ, RD, ADV, J + 1>(FA, FB, acc, C, R, L, lw, stage, RA, RB);
         }
     }
-    template <int H, bool ZERO, int Q0, int NQ, int RD = 0>
+    template <int H, bool ZERO, int Q0, int NQ, int RD, int ADV>
     static __device__ __forceinline__ void mma_half(const XFragA &FA, const XFragB &FB,
-                                                    floatx4 (&acc)[16][4], const Cursor &C,
+                                                    floatx4 (&acc)[16][4], Cursor &C, Ring &R,
                                                     const XLane &L, uint32_t lw,
                                                     const char *stage, XFragA &RA, XFragB &RB) {
-        mma_from<H, ZERO, Q0, NQ, RD, 0>(FA, FB, acc, C, L, lw, stage, RA, RB);
+        mma_from<H, ZERO, Q0, NQ, RD, ADV, 0>(FA, FB, acc, C, R, L, lw, stage, RA, RB);
         __builtin_amdgcn_sched_barrier(0);
     }
 
@@ -203,36 +232,54 @@ struct WidePipe {
         compiler_fence();
     }
 
-    // One step in stage st: meet the barrier, read the first half's A blocks and the B
-    // blocks, run the previous step's second half (PA x PB) under those reads, read this
-    // step's second-half A blocks into PA, run the first half. KIND 0: the block's first
-    // step (no pending half; the first half starts its accumulators at zero); KIND 1:
-    // its second step (the pending half starts its accumulators at zero); KIND 2: later.
+    // One step: meet the barrier, read the first half's A blocks and the B blocks (FB), run
+    // the previous step's second half (PA x PB) under those reads, read this step's
+    // second-half A blocks into PA, run the first half. KIND 0: the block's first step (no
+    // pending half; the first half starts its accumulators at zero); KIND 1: its second
+    // step (the pending half starts its accumulators at zero); KIND 2: later.
     template <int KIND>
-    static __device__ __forceinline__ void step(const Args &a, const XLane &L, Cursor &C,
-                                                int st, floatx4 (&acc)[16][4], XFragA &PA,
-                                                XFragB &PB) {
-        const int pv = st == 0 ? XNST - 1 : st - 1;
-        P::turn(C, a);
+    static __device__ __forceinline__ void step(const XLane &L, Cursor &C, Ring &R,
+                                                floatx4 (&acc)[16][4], XFragA &PA,
+                                                const XFragB &PB, XFragB &FB) {
         arrive();
-        const uint32_t lw = stage_w(L, pv);
-        const char *stage = x_ring + st * XSTAGE;
+        const uint32_t lw = stage_w(L, R.wr);
+        const char *stage = x_ring + R.rd;
         XFragA F0;
-        XFragB FB;
         if (KIND == 0) {
-            read_a<0>(L, st, F0);
-            read_b(L, st, FB);
-            read_a<1>(L, st, PA);
+            read_a<0>(L, stage, F0);
+            read_b(L, stage, FB);
+            read_a<1>(L, stage, PA);
             __builtin_amdgcn_sched_barrier(0);
-            mma_half<0, true, 0, 8>(F0, FB, acc, C, L, lw, stage, F0, FB);
+            mma_half<0, true, 0, 8, 0, 7>(F0, FB, acc, C, R, L, lw, stage, F0, FB);
         } else {
             // the previous step's second half, with this step's first reads in between
-            mma_half<1, KIND == 1, 0, 4, 1>(PA, PB, acc, C, L, lw, stage, F0, FB);
+            mma_half<1, KIND == 1, 0, 4, 1, 1>(PA, PB, acc, C, R, L, lw, stage, F0, FB);
             // this step's first half, with its second-half reads (into PA) in between
-            mma_half<0, false, 4, 4, 2>(F0, FB, acc, C, L, lw, stage, PA, FB);
+            mma_half<0, false, 4, 4, 2, 6>(F0, FB, acc, C, R, L, lw, stage, PA, FB);
         }
-        PB = FB;
-        P::advance(C);
+    }
+
+    // A block of `count` steps (even, at least 2) into acc. The prefetches run two steps
+    // ahead: the cursor turns to the next block before the last two steps. The block's last
+    // half runs after its last step.
+    static __device__ __forceinline__ void block(const Args &a, const XLane &L, Cursor &C,
+                                                 Ring &R, int count, floatx4 (&acc)[16][4]) {
+        XFragA PA;
+        XFragB B0, B1;
+        if (count == 2) P::turn(C, a);
+        step<0>(L, C, R, acc, PA, B1, B0);
+        step<1>(L, C, R, acc, PA, B0, B1);
+        if (count > 2) {
+            for (int k = 4; k < count; k += 2) {
+                step<2>(L, C, R, acc, PA, B1, B0);
+                step<2>(L, C, R, acc, PA, B0, B1);
+            }
+            P::turn(C, a);
+            step<2>(L, C, R, acc, PA, B1, B0);
+            step<2>(L, C, R, acc, PA, B0, B1);
+        }
+        mma_half<1, false, 0, 0, 0, 0>(PA, B1, acc, C, R, L, 0u, x_ring, PA, B1);
+        __builtin_amdgcn_sched_barrier(0);
     }
 };
 
