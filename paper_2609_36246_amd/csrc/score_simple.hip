@@ -82,7 +82,8 @@ __device__ __forceinline__ void fold16(const floatx16 &z, const floatx16 &o, GRu
         tm = fmaxf(tm, z[r]);
     }
     const float resc = exp_gap(R.st.best, tm, c);
-    float zs = R.st.z * resc, as = R.acc * resc;
+    // the block's sums first, then onto the column's: shorter chains of roundings
+    float zs = 0.f, as = 0.f;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
         const int v = v0 + 8 * (r >> 2) + (r & 3);
@@ -101,8 +102,8 @@ __device__ __forceinline__ void fold16(const floatx16 &z, const floatx16 &o, GRu
     R.st.best = tm;
     R.st.sec = ts;
     R.st.idx = idx;
-    R.st.z = zs;
-    R.acc = as;
+    R.st.z = fmaf(R.st.z, resc, zs);
+    R.acc = fmaf(R.acc, resc, as);
 }
 
 // Merge the record of a lane's column with that of another lane (the same rows' column).
@@ -197,7 +198,8 @@ score_simple_kernel(ScoreArgs a, int same_scale) {
         // One step's MFMAs from stage b: 4 groups of 8 K elements; the lane's half h takes
         // elements 8 q + 4 h .. + 3 of both operands. A group's fragments are read while
         // the previous one's MFMAs run.
-        auto compute = [&](int b, floatx16 (&acc)[2]) {
+        // Every other group goes to a second accumulator set (chains of d / 2 products).
+        auto compute = [&](int b, floatx16 (&acc)[2], floatx16 (&alt)[2]) {
             const float *sa = &stage[b][wid * 32 * SK], *sb = &stage[b][SIMPLE_VC * SK];
             float4 A = *(const float4 *)(sa + get_off[0]), B0 = *(const float4 *)(sb + get_off[0]),
                    B1 = *(const float4 *)(sb + 32 * SK + get_off[0]);
@@ -213,8 +215,9 @@ score_simple_kernel(ScoreArgs a, int same_scale) {
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[e], b0[e], acc[0], 0, 0, 0);
-                    acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[e], b1[e], acc[1], 0, 0, 0);
+                    floatx16 (&to)[2] = q & 1 ? alt : acc;
+                    to[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[e], b0[e], to[0], 0, 0, 0);
+                    to[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[e], b1[e], to[1], 0, 0, 0);
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -235,16 +238,19 @@ score_simple_kernel(ScoreArgs a, int same_scale) {
             // the unit ends)
             auto sweep = [&](int m, floatx16 (&acc)[2], int nc, int nm) {
                 const int d = HAS_T && m ? a.dt : a.ds;
+                floatx16 alt[2] = {floatx16{0.f}, floatx16{0.f}};
                 for (int k0 = 0; k0 < d; k0 += SK) {
                     // stage b is written; nobody reads stage b ^ 1 any more
                     __syncthreads();
                     const bool last = k0 + SK >= d, more = !last || nc >= 0;
                     if (last && more) enter(nc, nm);
                     if (more) fetch();
-                    compute(b, acc);
+                    compute(b, acc, alt);
                     b ^= 1;
                     if (more) put(b);
                 }
+                acc[0] += alt[0];
+                acc[1] += alt[1];
             };
             const int cn = c + 1 < c1 ? c + 1 : -1;
             sweep(0, accS, HAS_T ? c : cn, HAS_T ? 1 : 0);
