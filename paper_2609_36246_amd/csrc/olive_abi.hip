@@ -57,6 +57,8 @@ struct olive_score_ctx {
     uint16_t *bw_hrt = nullptr;                 // [d_S][chunk]
     float *bw_mref = nullptr;                   // [vocabulary tiles][chunk], then gy [chunk]
                                                 // and yrow [chunk] (int32)
+    float *bw_gws = nullptr;                    // partial tiles of the dL/dh product
+    int64_t bw_gtiles = 0;
     // Normalisers of the last forward call on the MFMA path and the batch they belong
     // to, for a backward on that batch (OLIVE_GRAD_REUSE_FORWARD). Scored rows take the
     // same compacted index in every pass (scored-first compaction), so the forward's
@@ -93,7 +95,7 @@ void release(olive_score_ctx *c) {
     void *ptrs[] = {c->ws_own, c->wt_own, c->rowmap, c->seqbuf, c->sched, c->part,
                     c->logp_tmp, c->lse_buf, c->flagged, c->fx_scratch, c->wn_s, c->wn_t, c->err,
                     c->tk_buf, c->fx_buf, c->bw_lse, c->bw_wt, c->bw_dzt, c->bw_hrt, c->bw_mref,
-                    c->wp_s, c->wp_t, c->hp_s, c->hp_t};
+                    c->bw_gws, c->wp_s, c->wp_t, c->hp_s, c->hp_t};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     delete c;
@@ -550,9 +552,9 @@ olive_status run_backward(olive_score_ctx *ctx, const olive_batch *b, const oliv
             g.trans_out = true;
             g.alpha = a.sS;
             g.accumulate = false;
-            // d_S / 256 x rows / 128 tiles rarely fill the grid: halve K over two units
-            // (the rows of dL/dh were zero-filled above)
-            g.ksplit = 2;
+            // d_S / 256 x rows / 128 tiles rarely fill the grid: K is split
+            g.ws = ctx->bw_gws;
+            g.ws_tiles = ctx->bw_gtiles;
             s = check_hip(launch_gemm(g, grid, st));
             if (s) return s;
         }
@@ -780,6 +782,14 @@ olive_status olive_score_init(olive_score_ctx **out, const olive_score_desc *des
         if (!s)
             s = dev_alloc(&c->bw_mref,
                           ((size_t)(V + 255) / 256 + 2) * c->bw_chunk * sizeof(float));
+        // a second part of every tile of a chunk's dL/dh product, and with few tiles as many
+        // parts as two rounds of the grid hold
+        const int64_t tiles = (ds + MFMA_BV - 1) / MFMA_BV *
+                              ((c->bw_chunk + MFMA_BT - 1) / MFMA_BT);
+        c->bw_gtiles = tiles > 2 * c->n_cu ? tiles : 2 * c->n_cu;
+        if (!s)
+            s = dev_alloc(&c->bw_gws,
+                          (size_t)c->bw_gtiles * MFMA_BV * MFMA_BT * sizeof(float));
         if (!s) s = backward_init(c, st);
     }
     c->wide = c->mfma_ok && !(d.flags & OLIVE_FLAG_NARROW_TILE);

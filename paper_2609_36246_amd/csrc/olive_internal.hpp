@@ -197,7 +197,8 @@ struct GemmArgs {
     float alpha;
     bool trans_out;              // C[n][m] instead of C[m][n]
     bool accumulate;             // C += instead of C =
-    int ksplit;                  // 1, or 2: halves of K added into C with atomics
+    float *ws;                   // or null: room for ws_tiles partial tiles of 256 x 128
+    int64_t ws_tiles;            // floats, K then split over as many units as pay
     // A given K-major instead: a_panels > 0 panels of 64 rows m, panel p holding K rows
     // of 128 bytes (64 m values each) at A + (p * a_prows + k) * 128 ([M/64][K][64]); the
     // MFMA operand is formed with LDS transpose reads. lda and akstep are then unused.

@@ -9,6 +9,7 @@ from oracle import olive_oracle as O
 from paper_2609_36246_amd import _lib as L
 from paper_2609_36246_amd import workloads as W
 from tests.gpu_harness import compare, run_hip, say, to_np
+from tests.test_gpu_backward import check_grads, oracle_backward, run_backward
 
 pytestmark = pytest.mark.gpu
 
@@ -80,6 +81,24 @@ def test_backward_of_few_rows_many_splits():
         bw = (2.0 ** -8 + T * 2.0 ** -24) * (ha[ref["rows"]].T @ ga) + 1e-6
         assert np.all(np.abs(to_np(gh)[ref["rows"]] - ref["grad_h"][ref["rows"]]) <= bh)
         assert np.all(np.abs(to_np(gw) - ref["grad_w"]) <= bw)
+
+
+# The dL/dh product splits K over more units where its tiles (256 of d_S x 128 rows) leave
+# compute units idle: one tile with few K steps (a part per step), ragged tiles in both
+# directions, a reduced tile count that fits no second part evenly, and two chunks of rows
+# (the second one short). The parts add in a fixed order: repeated calls are bit-identical.
+@pytest.mark.parametrize("T,ds,V", [(1, 64, 300), (129, 320, 20000), (700, 576, 3000),
+                                    (2900, 64, 1000), (8200, 128, 300)])
+def test_backward_product_splits(T, ds, V):
+    say("backward product", T, ds, V)
+    wl = custom("parts", num_seqs=1, seq_len=T, vocab=V, d_student=ds, d_teacher=64,
+                cut_rule=("frac", 0.0, 0.0))
+    hip = run_backward(wl, keep_ctx=True)
+    again = run_backward(wl, ctx=hip["ctx"])
+    L.olive_score_free(hip["ctx"])
+    for k in ("h", "w"):
+        np.testing.assert_array_equal(hip[k], again[k], err_msg=k)
+    check_grads(hip, oracle_backward(wl, 1.0, 0.0, O.REGION_TEACHER), wl, "product-%d" % T)
 
 
 # The generic kernel's tiles: 128 vocabulary rows x 64 positions, K in steps of 32 read in
