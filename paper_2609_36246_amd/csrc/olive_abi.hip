@@ -552,7 +552,7 @@ olive_status run_backward(olive_score_ctx *ctx, const olive_batch *b, const oliv
             g.trans_out = true;
             g.alpha = a.sS;
             g.accumulate = false;
-            // d_S / 256 x rows / 128 tiles rarely fill the grid: K is split
+            // d_S / 256 x rows / 256 tiles rarely fill the grid: K is split
             g.ws = ctx->bw_gws;
             g.ws_tiles = ctx->bw_gtiles;
             s = check_hip(launch_gemm(g, grid, st));
@@ -784,12 +784,12 @@ olive_status olive_score_init(olive_score_ctx **out, const olive_score_desc *des
                           ((size_t)(V + 255) / 256 + 2) * c->bw_chunk * sizeof(float));
         // a second part of every tile of a chunk's dL/dh product, and with few tiles as many
         // parts as two rounds of the grid hold
-        const int64_t tiles = (ds + MFMA_BV - 1) / MFMA_BV *
-                              ((c->bw_chunk + MFMA_BT - 1) / MFMA_BT);
+        const int64_t tiles = (ds + GEMM_TILE - 1) / GEMM_TILE *
+                              ((c->bw_chunk + GEMM_TILE - 1) / GEMM_TILE);
         c->bw_gtiles = tiles > 2 * c->n_cu ? tiles : 2 * c->n_cu;
         if (!s)
             s = dev_alloc(&c->bw_gws,
-                          (size_t)c->bw_gtiles * MFMA_BV * MFMA_BT * sizeof(float));
+                          (size_t)c->bw_gtiles * GEMM_TILE * GEMM_TILE * sizeof(float));
         if (!s) s = backward_init(c, st);
     }
     c->wide = c->mfma_ok && !(d.flags & OLIVE_FLAG_NARROW_TILE);

@@ -126,6 +126,7 @@ enum {
 constexpr int MFMA_BV = 256;     // vocabulary rows per tile (MFMA M)
 constexpr int MFMA_BT = 128;     // positions per tile (MFMA N)
 constexpr int WIDE_BT = 256;     // positions per tile of the 256 x 256 kernel
+constexpr int GEMM_TILE = 256;   // rows of either operand per tile of the products
 constexpr int SIMPLE_BT = 64;    // positions per tile of the generic kernel
 constexpr int SIMPLE_VC = 128;   // vocabulary rows per tile of the generic kernel
 constexpr int SIMPLE_WG = 2;     // its workgroups per compute unit (3 fit)
@@ -197,7 +198,7 @@ struct GemmArgs {
     float alpha;
     bool trans_out;              // C[n][m] instead of C[m][n]
     bool accumulate;             // C += instead of C =
-    float *ws;                   // or null: room for ws_tiles partial tiles of 256 x 128
+    float *ws;                   // or null: room for ws_tiles partial tiles of 256 x 256
     int64_t ws_tiles;            // floats, K then split over as many units as pay
     // A given K-major instead: a_panels > 0 panels of 64 rows m, panel p holding K rows
     // of 128 bytes (64 m values each) at A + (p * a_prows + k) * 128 ([M/64][K][64]); the
