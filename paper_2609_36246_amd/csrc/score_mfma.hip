@@ -218,31 +218,42 @@ struct Kernel {
         }
     }
 
-    // The 8 MFMAs of one sub-step with DMAs Q0 .. Q0+NQ-1 of the step's refill spread
-    // between them. Each 1 KB DMA holds the CU's address path for about 16 cycles, so
-    // the refill is spread over the whole step: issued in a burst, the DMAs back up
-    // and stall the wave in front of its next MFMA.
-    template <bool NORM, int Q0, int NQ>
-    static __device__ __forceinline__ void mma_issue(const Frag &F, floatx16 (&acc)[4][2],
-                                                     float (&nsq)[4], const Cursor &C,
-                                                     uint32_t lw, uint32_t lh) {
-#define OLIVE_MI(J_, VB_, CB_)                                                             \
-        __builtin_amdgcn_sched_barrier(0);                                               \
-        acc[VB_][CB_] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(F.A[VB_], F.B[CB_],        \
-                                                                acc[VB_][CB_], 0, 0, 0); \
-        __builtin_amdgcn_sched_barrier(0);                                               \
-        if constexpr (NORM) nsq[VB_] = add_squares<CB_>(F.A[VB_], nsq[VB_]);               \
-        dmas<Q0 + ((J_) * NQ + 7) / 8, Q0 + ((J_) * NQ + NQ + 7) / 8>(C, lw, lh);
-        OLIVE_MI(0, 0, 0)
-        OLIVE_MI(1, 0, 1)
-        OLIVE_MI(2, 1, 0)
-        OLIVE_MI(3, 1, 1)
-        OLIVE_MI(4, 2, 0)
-        OLIVE_MI(5, 2, 1)
-        OLIVE_MI(6, 3, 0)
-        OLIVE_MI(7, 3, 1)
-#undef OLIVE_MI
-        __builtin_amdgcn_sched_barrier(0);
+    // Read J of sub-step SUB's fragments: A block 0 and the B blocks first.
+    template <int SUB, int J>
+    static __device__ __forceinline__ void read_at(const Lane &L, const char *stage, Frag &F) {
+        if constexpr (SUB < 4 && (J == 1 || J == 2))
+            F.B[J - 1] = *(const bf16x8 *)(stage + WT_BYTES + L.wt * 64 * ROWB + L.ldsoff[SUB] +
+                                           (J - 1) * 32 * ROWB);
+        else if constexpr (SUB < 4 && J < 6) {
+            constexpr int vb = J == 0 ? 0 : J - 2;
+            F.A[vb] = *(const bf16x8 *)(stage + L.wv * 128 * ROWB + L.ldsoff[SUB] +
+                                        vb * 32 * ROWB);
+        }
+    }
+
+    // The 8 MFMAs of one sub-step (fragments F); behind each of the first 6 one read of
+    // sub-step SUB's fragments into R (SUB 4: none), and DMAs Q0 .. Q0+NQ-1 of the step's
+    // refill spread between them. Each 1 KB DMA holds the CU's address path for about 16
+    // cycles, so the refill is spread over the whole step: issued in a burst, the DMAs back
+    // up and stall the wave in front of its next MFMA.
+    template <bool NORM, int Q0, int NQ, int SUB, int J>
+    static __device__ __forceinline__ void mma_from(const Frag &F, floatx16 (&acc)[4][2],
+                                                    float (&nsq)[4], const Cursor &C,
+                                                    uint32_t lw, uint32_t lh, const Lane &L,
+                                                    const char *stage, Frag &R) {
+        if constexpr (J < 8) {
+            constexpr int vb = J >> 1, cb = J & 1;
+            __builtin_amdgcn_sched_barrier(0);
+            acc[vb][cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(F.A[vb], F.B[cb], acc[vb][cb],
+                                                                  0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            read_at<SUB, J>(L, stage, R);
+            if constexpr (NORM) nsq[vb] = add_squares<cb>(F.A[vb], nsq[vb]);
+            dmas<Q0 + (J * NQ + 7) / 8, Q0 + (J * NQ + NQ + 7) / 8>(C, lw, lh);
+            mma_from<NORM, Q0, NQ, SUB, J + 1>(F, acc, nsq, C, lw, lh, L, stage, R);
+        } else {
+            __builtin_amdgcn_sched_barrier(0);
+        }
     }
 
     // Stage barrier at the start of step n: wait until this wave's DMAs of step n have
@@ -259,11 +270,14 @@ struct Kernel {
 
     // One pipeline step n in stage `st`: meet the stage barrier, prefetch the cursor's
     // step (n+2) into the stage of step n-1, then run the step's four k16 sub-steps,
-    // each one's LDS reads issued under the previous one's MFMAs. With PEND, the last
+    // each one's LDS reads interleaved with the previous one's MFMAs. With PEND, the last
     // sub-step of step n-1 (fragments in P) runs under the first reads. On return P
     // holds this step's last sub-step, still to be run. Every step issues its 12 DMAs
     // (past the end of a unit, those of its last step again), so no DMA sits under a
-    // branch.
+    // branch. (One read behind each MFMA, against a sub-step's 6 reads in a burst before
+    // its predecessor's MFMAs: the monitoring report of 3124 positions, V = 151936, d 1536
+    // + 3584, 7.86 -> 7.64 ms; 771 positions without a context 1.47 -> 1.43; and the
+    // top-K instances no longer spill with equal scales.)
     template <bool PEND, bool NORM>
     static __device__ __forceinline__ void step(const ScoreArgs &a, const Lane &L, Cursor &C,
                                                 int st, floatx16 (&acc)[4][2], float (&nsq)[4],
@@ -272,30 +286,18 @@ struct Kernel {
         turn(C, a, L);
         arrive();
         const uint32_t lw = stage_w(L, pv), lh = stage_h(L, pv);
-        Frag F0, F1, F2;
-        read_frag<0>(L, st, F0);
-        __builtin_amdgcn_sched_barrier(0);
+        const char *stage = g_ring + st * STAGE_BYTES;
+        Frag F0, F1;
         if (PEND) {
-            mma_issue<NORM, 0, 3>(P, acc, nsq, C, lw, lh);
-            read_frag<1>(L, st, F1);
-            __builtin_amdgcn_sched_barrier(0);
-            mma_issue<NORM, 3, 3>(F0, acc, nsq, C, lw, lh);
-            read_frag<2>(L, st, F2);
-            __builtin_amdgcn_sched_barrier(0);
-            mma_issue<NORM, 6, 3>(F1, acc, nsq, C, lw, lh);
-            read_frag<3>(L, st, P);
-            __builtin_amdgcn_sched_barrier(0);
-            mma_issue<NORM, 9, 3>(F2, acc, nsq, C, lw, lh);
+            mma_from<NORM, 0, 3, 0, 0>(P, acc, nsq, C, lw, lh, L, stage, F0);
+            mma_from<NORM, 3, 3, 1, 0>(F0, acc, nsq, C, lw, lh, L, stage, F1);
+            mma_from<NORM, 6, 3, 2, 0>(F1, acc, nsq, C, lw, lh, L, stage, F0);
+            mma_from<NORM, 9, 3, 3, 0>(F0, acc, nsq, C, lw, lh, L, stage, P);
         } else {
-            read_frag<1>(L, st, F1);
-            __builtin_amdgcn_sched_barrier(0);
-            mma_issue<NORM, 0, 4>(F0, acc, nsq, C, lw, lh);
-            read_frag<2>(L, st, F2);
-            __builtin_amdgcn_sched_barrier(0);
-            mma_issue<NORM, 4, 4>(F1, acc, nsq, C, lw, lh);
-            read_frag<3>(L, st, P);
-            __builtin_amdgcn_sched_barrier(0);
-            mma_issue<NORM, 8, 4>(F2, acc, nsq, C, lw, lh);
+            read_frag<0>(L, st, F0);
+            mma_from<NORM, 0, 4, 1, 0>(F0, acc, nsq, C, lw, lh, L, stage, F1);
+            mma_from<NORM, 4, 4, 2, 0>(F1, acc, nsq, C, lw, lh, L, stage, F0);
+            mma_from<NORM, 8, 4, 3, 0>(F0, acc, nsq, C, lw, lh, L, stage, P);
         }
         advance(C);
     }
