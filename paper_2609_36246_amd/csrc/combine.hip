@@ -8,9 +8,16 @@
 //   kl_rev = B / Z_S - lse_S + lse_T   (KL(student || teacher), in-region only),
 //   argmax_X = lowest index attaining the max,
 // queueing rows whose top-2 gap is inside the fp32 error window for the exact
-// re-decision of their greedy token.
+// re-decision of their greedy token (on the MFMA path straight into its filter's queue).
+//
+// Bound by latency: a row's loads depend on one another three deep (row, token, weight
+// row), so the split records are fetched before the dot products and everything a wavefront
+// reads comes in 16-byte pieces. 160 positions at V = 151936 in 198 splits: 19 us, 4096 at V
+// = 32000 21 us; with the records after the products, 2-byte loads in the rounding bounds
+// and the queue in a kernel of its own 29 and 43 us.
 #include <hip/hip_runtime.h>
 
+#include "fx_queue.hpp"
 #include "olive_device.hpp"
 #include "olive_internal.hpp"
 
@@ -34,6 +41,7 @@ __device__ __forceinline__ float wave_dot<uint16_t>(const uint16_t *h, const uin
     if ((d & 7) == 0 && ((uintptr_t)h & 15) == 0 && ((uintptr_t)w & 15) == 0) {
         const uint4 *h4 = (const uint4 *)h;
         const uint4 *w4 = (const uint4 *)w;
+#pragma unroll 4
         for (int i = lane; i < (d >> 3); i += 64) {
             uint4 x = h4[i], y = w4[i];
             uint32_t xs[4] = {x.x, x.y, x.z, x.w}, ys[4] = {y.x, y.y, y.z, y.w};
@@ -64,8 +72,25 @@ __device__ __forceinline__ float wave_dot<float>(const float *h, const float *w,
 template <typename E>
 __device__ __forceinline__ float wave_absdot(const E *h, const E *w, int d, int lane) {
     float acc = 0.f;
-    for (int k = lane; k < d; k += 64)
-        acc = fmaf(fabsf(load_elem(h, k)), fabsf(load_elem(w, k)), acc);
+    if (sizeof(E) == 2 && (d & 7) == 0 && (((uintptr_t)h | (uintptr_t)w) & 15) == 0) {
+        const uint4 *h4 = (const uint4 *)h;
+        const uint4 *w4 = (const uint4 *)w;
+#pragma unroll 4
+        for (int i = lane; i < (d >> 3); i += 64) {
+            const uint4 x = h4[i], y = w4[i];
+            const uint32_t xs[4] = {x.x, x.y, x.z, x.w}, ys[4] = {y.x, y.y, y.z, y.w};
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                acc = fmaf(fabsf(__uint_as_float(xs[q] << 16)),
+                           fabsf(__uint_as_float(ys[q] << 16)), acc);
+                acc = fmaf(fabsf(__uint_as_float(xs[q] & 0xffff0000u)),
+                           fabsf(__uint_as_float(ys[q] & 0xffff0000u)), acc);
+            }
+        }
+    } else {
+        for (int k = lane; k < d; k += 64)
+            acc = fmaf(fabsf(load_elem(h, k)), fabsf(load_elem(w, k)), acc);
+    }
     for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
     return acc;
 }
@@ -123,7 +148,8 @@ combine_kernel(ScoreArgs a, int same_scale, const int32_t *__restrict__ targets,
                int32_t *__restrict__ err, float *__restrict__ logp_s, float *__restrict__ logp_t,
                int32_t *__restrict__ am_s, int32_t *__restrict__ am_t, float *__restrict__ kl,
                float *__restrict__ kl_rev, float *__restrict__ logp_tmp,
-               float *__restrict__ lse_out, int32_t *__restrict__ flagged, int flag_cap) {
+               float *__restrict__ lse_out, int32_t *__restrict__ flagged, int flag_cap,
+               FilterQueue fq) {
     const int lane = threadIdx.x & 63;
     const int64_t j = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     Sched *sched = const_cast<Sched *>(a.sched);
@@ -147,6 +173,24 @@ combine_kernel(ScoreArgs a, int same_scale, const int32_t *__restrict__ targets,
         }
         return;
     }
+    const int ns = sched->n_splits;
+    Stat ss = stat_identity(), st = stat_identity();
+    float acc_a = 0.f, acc_b = 0.f, acc_zh = 0.f;
+    // the 256 x 256 kernel's fp16 weight sums follow the model whose weights it kept
+    const bool zh_s = HAS_T && a.wide == 2, zh_t = HAS_T && a.wide == 1;
+    const int64_t fs = a.fstride, ps = sched->pstride;
+    auto record = [&](int s, Stat &s1, Stat &t1, float &a1, float &b1, float &z1) {
+        const float *P = a.part + s * ps + j;
+        s1 = load_stat(P, fs, F_BEST_S);
+        if (HAS_T) {
+            t1 = load_stat(P, fs, F_BEST_T);
+            if (kl) a1 = P[F_A * fs];
+            if (kl_rev) b1 = P[F_B * fs];
+            if (a.wide) z1 = P[F_ZH * fs];
+        }
+    };
+    // lane l takes splits l, l + 64, ... in order
+    if (lane < ns) record(lane, ss, st, acc_a, acc_b, acc_zh);
     const E *hs = (const E *)a.hs;
     const E *ws = (const E *)a.ws;
     const float zy_s = wave_dot<E>(hs + g * a.ds, ws + (int64_t)y * a.ds, a.ds, lane);
@@ -156,28 +200,10 @@ combine_kernel(ScoreArgs a, int same_scale, const int32_t *__restrict__ targets,
         const E *wt = (const E *)a.wt;
         zy_t = wave_dot<E>(ht + g * a.dt, wt + (int64_t)y * a.dt, a.dt, lane);
     }
-    const int ns = sched->n_splits;
-    Stat ss = stat_identity(), st = stat_identity();
-    float acc_a = 0.f, acc_b = 0.f, acc_zh = 0.f;
-    // the 256 x 256 kernel's fp16 weight sums follow the model whose weights it kept
-    const bool zh_s = HAS_T && a.wide == 2, zh_t = HAS_T && a.wide == 1;
-    // lane l takes splits l, l + 64, ... in order
-    const int64_t fs = a.fstride, ps = sched->pstride;
-    for (int s = lane; s < ns; s += 64) {
-        const float *P = a.part + s * ps + j;
-        Stat s1 = load_stat(P, fs, F_BEST_S), t1 = stat_identity();
+    for (int s = lane + 64; s < ns; s += 64) {
+        Stat s1, t1 = stat_identity();
         float a1 = 0.f, b1 = 0.f, z1 = 0.f;
-        if (HAS_T) {
-            t1 = load_stat(P, fs, F_BEST_T);
-            if (kl) a1 = P[F_A * fs];
-            if (kl_rev) b1 = P[F_B * fs];
-            if (a.wide) z1 = P[F_ZH * fs];
-        }
-        if (s < 64) {
-            ss = s1; st = t1;
-            acc_a = a1; acc_b = b1; acc_zh = z1;
-            continue;
-        }
+        record(s, s1, t1, a1, b1, z1);
         Stat w = zh_s ? ss : st;   // the weight sum follows the same rescale
         if (zh_s) stat_merge(w, acc_zh, s1, z1, a.cS);
         if (zh_t) stat_merge(w, acc_zh, t1, z1, a.cT);
@@ -205,6 +231,10 @@ combine_kernel(ScoreArgs a, int same_scale, const int32_t *__restrict__ targets,
             const E *wt = (const E *)a.wt;
             float za = wave_absdot<E>(ht + g * a.dt, wt + (int64_t)st.idx * a.dt, a.dt, lane);
             theta_t = st.best - (float)a.dt * (1.0f / 8388608.0f) * za;
+        }
+        if (sizeof(E) == 2 && fq.n) {
+            if (fl & 1) fx_queue_pair(a, fq, 0, j, g, theta_s, ns, lane);
+            if (HAS_T && (fl & 2)) fx_queue_pair(a, fq, 1, j, g, theta_t, ns, lane);
         }
     }
     if (lane != 0) return;
@@ -234,10 +264,10 @@ combine_kernel(ScoreArgs a, int same_scale, const int32_t *__restrict__ targets,
             kl_rev[g] = inr ? v : 0.f;
         }
     }
-    if (fl && flagged) {
+    if (fl) {
         int q = atomicAdd(&sched->n_flagged, 1);
         atomicOr(&sched->fl_models, (uint32_t)fl);
-        if (q < flag_cap) {
+        if (flagged && q < flag_cap) {
             flagged[4 * q] = (int32_t)j;
             flagged[4 * q + 1] = fl;
             flagged[4 * q + 2] = __float_as_int(theta_s);
@@ -379,15 +409,15 @@ hipError_t launch_jsd_combine(const ScoreArgs &a, float *jsd, int64_t max_rows,
 hipError_t launch_combine(const ScoreArgs &a, bool bf16, bool has_t, bool same_scale,
                           const int32_t *targets, int32_t *err, float *logp_s, float *logp_t,
                           int32_t *am_s, int32_t *am_t, float *kl, float *kl_rev, float *logp_tmp,
-                          float *lse_out, int32_t *flagged, int flag_cap, int64_t max_rows,
-                          hipStream_t st) {
+                          float *lse_out, int32_t *flagged, int flag_cap,
+                          const FilterQueue &fq, int64_t max_rows, hipStream_t st) {
     if (max_rows <= 0) return hipSuccess;
     dim3 grid((unsigned)((max_rows + 3) / 4));
     int same = same_scale ? 1 : 0;
 #define OLIVE_COMBINE(E_, T_)                                                                \
     combine_kernel<E_, T_><<<grid, 256, 0, st>>>(a, same, targets, err, logp_s, logp_t, am_s, \
                                                  am_t, kl, kl_rev, logp_tmp, lse_out, flagged,   \
-                                                 flag_cap)
+                                                 flag_cap, fq)
     if (bf16) {
         if (has_t) OLIVE_COMBINE(uint16_t, true);
         else OLIVE_COMBINE(uint16_t, false);

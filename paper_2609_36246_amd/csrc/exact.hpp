@@ -102,12 +102,19 @@ __device__ __forceinline__ void wave_exact_list(const uint16_t *h, const uint16_
     }
 }
 
-// |h|^2 in fp32 by one wavefront.
+// |h|^2 in fp32 by one wavefront (d a multiple of 8, h 16-byte aligned).
 __device__ __forceinline__ float wave_sumsq(const uint16_t *h, int d, int lane) {
     float acc = 0.f;
-    for (int k = lane; k < d; k += 64) {
-        const float x = bf16_bits_to_f32(h[k]);
-        acc = fmaf(x, x, acc);
+    for (int k = lane * 8; k < d; k += 512) {
+        const uint4 x = *(const uint4 *)(h + k);
+        const uint32_t xs[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const float lo = __uint_as_float(xs[q] << 16);
+            const float hi = __uint_as_float(xs[q] & 0xffff0000u);
+            acc = fmaf(lo, lo, acc);
+            acc = fmaf(hi, hi, acc);
+        }
     }
     for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
     return acc;

@@ -269,11 +269,7 @@ olive_status run(olive_score_ctx *ctx, const olive_batch *b, const olive_spans *
 
     if (wide) {
         // the call's compacted hidden rows into panels (zero past them, to the tile end)
-        s = check_hip(launch_panel_h(b->h_student, d.d_student, ctx->rowmap, ctx->sched,
-                                     ctx->hp_rows, ctx->hp_s, st));
-        if (!s && has_t)
-            s = check_hip(launch_panel_h(b->h_teacher, d.d_teacher, ctx->rowmap, ctx->sched,
-                                         ctx->hp_rows, ctx->hp_t, st));
+        s = check_hip(launch_panel_h(a, st));
         if (s) return s;
     }
     const int slot = (int)(ctx->n_calls % 64);
@@ -291,11 +287,14 @@ olive_status run(olive_score_ctx *ctx, const olive_batch *b, const olive_spans *
     ctx->last_kernel = wide ? 2 : (mfma ? 0 : 1);
     ctx->last_grid = grid;
 
-    int32_t *flagged = (am_s || (has_t && am_t)) ? ctx->flagged : nullptr;
+    // near ties: the generic path lists the rows, the MFMA path queues them
+    const bool flagging = am_s || (has_t && am_t);
+    int32_t *flagged = flagging && !mfma ? ctx->flagged : nullptr;
+    const FilterQueue fq = flagging && mfma ? ctx->fxq : FilterQueue{};
     s = check_hip(launch_combine(a, ctx->bf16, has_t, same_scale, b->targets, ctx->err, logp_s,
                                  has_t ? logp_t : nullptr, am_s, has_t ? am_t : nullptr,
                                  has_t ? kl : nullptr, has_t ? kl_rev : nullptr, logp_tmp,
-                                 lse_out, flagged, ctx->flag_cap, T, st));
+                                 lse_out, flagged, ctx->flag_cap, fq, T, st));
     if (s) return s;
     if (mfma && ctx->bw && lse_out) {
         ctx->fwd_lse = lse_out;
@@ -305,10 +304,9 @@ olive_status run(olive_score_ctx *ctx, const olive_batch *b, const olive_spans *
         ctx->fwd_spans = spans != nullptr;
         if (spans) ctx->fwd_sp = *spans;
     }
-    if (flagged) {
+    if (flagging) {
         if (mfma)
-            s = check_hip(launch_argmax_fix(a, flagged, ctx->flag_cap, ctx->fxq, am_s,
-                                            has_t ? am_t : nullptr, st));
+            s = check_hip(launch_argmax_fix(a, fq, am_s, has_t ? am_t : nullptr, st));
         else if (ctx->no_init &&   // the rounding bounds of the flagged rows' candidates
                  (launch_row_norms(a.ws, V, a.ds, ctx->bf16, ctx->wn_s, ctx->sched, 1u, st) !=
                       hipSuccess ||
@@ -436,11 +434,7 @@ olive_status run_backward(olive_score_ctx *ctx, const olive_batch *b, const oliv
         // reuse (always, wherever that call's are kept: one rule for every output set)
         ctx->fwd_lse_ok = false;
         if (wide) {
-            s = check_hip(launch_panel_h(b->h_student, d.d_student, ctx->rowmap, ctx->sched,
-                                         ctx->hp_rows, ctx->hp_s, st));
-            if (!s && has_t)
-                s = check_hip(launch_panel_h(b->h_teacher, d.d_teacher, ctx->rowmap,
-                                             ctx->sched, ctx->hp_rows, ctx->hp_t, st));
+            s = check_hip(launch_panel_h(a, st));
             if (!s) s = check_hip(launch_score_wide(a, same_scale, has_t, false, grid, st));
         } else {
             s = check_hip(launch_score_mfma(a, has_t, same_scale, false, false, false, grid,
@@ -449,7 +443,7 @@ olive_status run_backward(olive_score_ctx *ctx, const olive_batch *b, const oliv
         if (s) return s;
         s = check_hip(launch_combine(a, true, has_t, same_scale, b->targets, ctx->err, nullptr,
                                      nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
-                                     ctx->bw_lse, nullptr, 0, T, st));
+                                     ctx->bw_lse, nullptr, 0, FilterQueue{}, T, st));
         if (s) return s;
         lse = ctx->bw_lse;
         if (wide) {
@@ -467,8 +461,7 @@ olive_status run_backward(olive_score_ctx *ctx, const olive_batch *b, const oliv
     // the hidden-row panels of every scored row (built by the normaliser pass, or here
     // when there was none)
     if (wide_dz && (!wide || online)) {
-        s = check_hip(launch_panel_h(b->h_student, d.d_student, ctx->rowmap, ctx->sched,
-                                     ctx->hp_rows, ctx->hp_s, st));
+        s = check_hip(launch_panel_h(a, st));
         if (s) return s;
     }
     // scored rows <= T: chunks past the call's positions are never launched (those past
@@ -489,7 +482,7 @@ olive_status run_backward(olive_score_ctx *ctx, const olive_batch *b, const oliv
         if (wide_dz) {
             ScoreArgs aw = a;
             aw.wps = ctx->wp_s;
-            aw.hps = (const char *)ctx->hp_s + c0 * 64;   // panel row c0 (32 bf16 per row)
+            aw.hps = (char *)ctx->hp_s + c0 * 64;   // panel row c0 (32 bf16 per row)
             aw.vpad = ctx->wp_rows;
             aw.prow = ctx->hp_rows;
             if (online) {
@@ -631,7 +624,7 @@ bool static_carve(olive_score_ctx *c, char *base) {
     c->wn_t = (float *)take((size_t)kStaticMaxVocab * sizeof(float));
     if (off > kStaticScratchBytes) return false;
     c->fxq = filter_queue_carve(c->fx_buf, c->flag_cap, FX_CCAP, &c->sched->n_fxq[0],
-                                &c->sched->n_fx_fb);
+                                nullptr);
     c->fxq.smask = &c->sched->fx_smask[0][0];
     return true;
 }
@@ -766,7 +759,7 @@ olive_status olive_score_init(olive_score_ctx **out, const olive_score_desc *des
         s = dev_alloc(&c->fx_buf, filter_queue_bytes(c->flag_cap, FX_CCAP));
         if (!s) {
             c->fxq = filter_queue_carve(c->fx_buf, c->flag_cap, FX_CCAP, &c->sched->n_fxq[0],
-                                        &c->sched->n_fx_fb);
+                                        nullptr);
             c->fxq.smask = &c->sched->fx_smask[0][0];   // the greedy filter reads marked splits
         }
     }

@@ -48,12 +48,12 @@ constexpr int FX_CCAP = 64;  // candidates kept per near-tie pair of the greedy 
 // candidates (launch_filter). Carved from one allocation (filter_queue_carve).
 struct FilterQueue {
     int32_t *n;          // device [2]: queued pairs per model (Sched fields)
-    int32_t *nfb;        // device: pairs sent to the exhaustive scan (a Sched field)
+    int32_t *nfb;        // device: pairs sent to the exhaustive scan (a Sched field; top-K)
     int32_t *qj;         // [2][cap] compacted row
     float *qthr;         // [2][cap] fp32 threshold on the raw logit h . w
     int32_t *qcnt;       // [2][cap] candidates found (may exceed ccap)
     int32_t *cand;       // [2][cap][ccap] their vocabulary indices
-    int32_t *fb;         // [2 cap] (model * cap + slot) of the pairs for the exhaustive scan
+    int32_t *fb;         // [2 cap] (model * cap + slot) of those pairs
     uint32_t *smask;     // device [2][SPLIT_WORDS] or null: per model, the vocabulary splits
                          // (bit s % 32 of word s / 32) the filter reads; null: every split
     int cap, ccap;
@@ -100,7 +100,6 @@ struct alignas(16) Sched {
     int32_t n_tkq[2];   // (row, model) pairs whose top-K field needs the vocabulary filter
     int32_t n_tk_fb;    // pairs of those that need the exhaustive exact scan
     int32_t n_fxq[2];   // near-tie (row, model) pairs of the greedy re-decision (MFMA path)
-    int32_t n_fx_fb;    // pairs of those that need the exhaustive exact scan
     uint32_t fx_smask[2][SPLIT_WORDS];   // per model: vocabulary splits (bit s % 32 of word
                                          // s / 32) the re-decision's filter must read
 };
@@ -147,7 +146,8 @@ struct ScoreArgs {
                                  // (used instead of wmax_s / wmax_t when set)
     // 256 x 256 kernel: K-blocked panels [d/32][rows][32] of the weights (rows = vpad,
     // zero past V) and of the call's compacted hidden rows (rows = prow)
-    const void *wps, *wpt, *hps, *hpt;
+    const void *wps, *wpt;
+    void *hps, *hpt;
     int64_t vpad, prow;
     int32_t wide;                // the partials come from that kernel: 1, KL(T || S)'s cross
                                  // term is A / ZH; 2 (reverse only), KL(S || T)'s is B / ZH
@@ -246,8 +246,7 @@ hipError_t launch_dz_rescale(const ScoreArgs &a, const DzArgs &z, const float *l
                              hipStream_t st);
 hipError_t launch_panel_w(const void *w, int64_t V, int d, int64_t vpad, void *out,
                           hipStream_t st);
-hipError_t launch_panel_h(const void *h, int d, const uint32_t *rowmap, const Sched *sched,
-                          int64_t prow, void *out, hipStream_t st);
+hipError_t launch_panel_h(const ScoreArgs &a, hipStream_t st);
 hipError_t launch_score_dz(const ScoreArgs &a, const DzArgs &z, bool has_t, int grid,
                            hipStream_t st);
 hipError_t launch_score_jsd(const ScoreArgs &a, const JsdArgs &z, int grid, hipStream_t st);
@@ -264,13 +263,12 @@ hipError_t launch_zero_tail(uint16_t *dzt, int64_t vp, int chunk, const Sched *s
 hipError_t launch_combine(const ScoreArgs &a, bool bf16, bool has_t, bool same_scale,
                           const int32_t *targets, int32_t *err, float *logp_s, float *logp_t,
                           int32_t *am_s, int32_t *am_t, float *kl, float *kl_rev, float *logp_tmp,
-                          float *lse_out, int32_t *flagged, int flag_cap, int64_t max_rows,
-                          hipStream_t st);
+                          float *lse_out, int32_t *flagged, int flag_cap,
+                          const FilterQueue &fq, int64_t max_rows, hipStream_t st);
 hipError_t launch_topk(const ScoreArgs &a, const TopkWork &w, const TopkOut &out,
                        int64_t max_rows, hipStream_t st);
-hipError_t launch_argmax_fix(const ScoreArgs &a, const int32_t *flagged, int flag_cap,
-                             const FilterQueue &q, int32_t *am_s, int32_t *am_t,
-                             hipStream_t st);
+hipError_t launch_argmax_fix(const ScoreArgs &a, const FilterQueue &q, int32_t *am_s,
+                             int32_t *am_t, hipStream_t st);
 hipError_t launch_fixup_impl(const ScoreArgs &a, bool bf16, const int32_t *flagged, int f_base,
                              int cap, void *scratch, const float *wn_s, const float *wn_t,
                              int32_t *am_s, int32_t *am_t, hipStream_t st);

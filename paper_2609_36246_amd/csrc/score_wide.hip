@@ -703,23 +703,27 @@ panel_w_kernel(const uint16_t *__restrict__ w, int64_t V, int d, int64_t vpad,
     *(uint4 *)(out + ((int64_t)pnl * vpad + v) * XK + panel_slot(v, q) * 8) = val;
 }
 
-// The compacted hidden rows of a call -> K-blocked panels [d/32][prow][32], chunks in
-// their swizzled slots: row j < t_valid is hidden row rowmap[j]; rows t_valid .. up to
-// the next multiple of 256 are zero (the last position tile's columns past the rows).
+// The compacted hidden rows of a call, of both models -> K-blocked panels [d/32][prow][32],
+// chunks in their swizzled slots: row j < t_valid is hidden row rowmap[j]; rows t_valid ..
+// up to the next multiple of 256 are zero (the last position tile's columns past the rows).
+// Block (64-row group, panel: the student's, then the teacher's).
 __global__ void __launch_bounds__(256)
-panel_h_kernel(const uint16_t *__restrict__ h, int d, const uint32_t *__restrict__ rowmap,
-               const Sched *__restrict__ sched, int64_t prow, uint16_t *__restrict__ out) {
-    const int t_valid = sched->t_valid;
+panel_h_kernel(ScoreArgs a) {
+    const int t_valid = a.sched->t_valid;
     const int64_t tpad = ((int64_t)t_valid + XT - 1) / XT * XT;
     const int64_t j = (int64_t)blockIdx.x * 64 + (threadIdx.x >> 2);
-    if (j >= tpad || j >= prow) return;
-    const int pnl = blockIdx.y, q = threadIdx.x & 3;
+    if (j >= tpad || j >= a.prow) return;
+    const int nS = a.ds / XK, q = threadIdx.x & 3;
+    const bool t = (int)blockIdx.y >= nS;
+    const int pnl = t ? blockIdx.y - nS : blockIdx.y, d = t ? a.dt : a.ds;
+    const uint16_t *h = (const uint16_t *)(t ? a.ht : a.hs);
+    uint16_t *out = (uint16_t *)(t ? a.hpt : a.hps);
     uint4 val = make_uint4(0u, 0u, 0u, 0u);
     if (j < t_valid) {
-        const int64_t g = rowmap[j] & 0x7fffffffu;
+        const int64_t g = a.rowmap[j] & 0x7fffffffu;
         val = *(const uint4 *)(h + g * d + pnl * XK + q * 8);
     }
-    *(uint4 *)(out + ((int64_t)pnl * prow + j) * XK + panel_slot(j, q) * 8) = val;
+    *(uint4 *)(out + ((int64_t)pnl * a.prow + j) * XK + panel_slot(j, q) * 8) = val;
 }
 
 }  // namespace
@@ -772,12 +776,11 @@ hipError_t launch_panel_w(const void *w, int64_t V, int d, int64_t vpad, void *o
     return hipGetLastError();
 }
 
-hipError_t launch_panel_h(const void *h, int d, const uint32_t *rowmap, const Sched *sched,
-                          int64_t prow, void *out, hipStream_t st) {
-    if (d % XK != 0 || prow % XT != 0) return hipErrorInvalidValue;
-    dim3 grid((unsigned)(prow / 64), (unsigned)(d / XK));
-    panel_h_kernel<<<grid, 256, 0, st>>>((const uint16_t *)h, d, rowmap, sched, prow,
-                                         (uint16_t *)out);
+// a.ds (and a.dt, 0: no teacher) wide rows of a.hs, a.ht into a.hps, a.hpt.
+hipError_t launch_panel_h(const ScoreArgs &a, hipStream_t st) {
+    if (a.ds % XK != 0 || a.dt % XK != 0 || a.prow % XT != 0) return hipErrorInvalidValue;
+    dim3 grid((unsigned)(a.prow / 64), (unsigned)((a.ds + a.dt) / XK));
+    panel_h_kernel<<<grid, 256, 0, st>>>(a);
     return hipGetLastError();
 }
 

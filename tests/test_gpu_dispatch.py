@@ -203,3 +203,23 @@ def test_topk_with_many_splits(T):
     plain = run_hip(wl, outputs=o)
     for k in ("kl", "kl_rev", "logp_s", "logp_t", "am_s", "am_t"):
         np.testing.assert_array_equal(hip[k], plain[k], err_msg=k)
+
+
+# The greedy re-decision on the MFMA path: exact ties of the teacher's winner with up to 64
+# candidates (decided from the queue), with more (the exhaustive scan, by the workgroup that
+# finds the overflow), on rows that fill a workgroup's four wavefronts, fewer and more.
+@pytest.mark.parametrize("ties,T", [(2, 1), (3, 9), (64, 5), (65, 1), (300, 3), (300, 9)])
+@pytest.mark.parametrize("narrow", [False, True], ids=["wide", "narrow"])
+def test_greedy_ties_beyond_the_queue(ties, T, narrow):
+    say("greedy ties", ties, T, narrow)
+    V = 3001
+    wl = custom("ties", num_seqs=1, seq_len=T, vocab=V, d_student=64, d_teacher=128,
+                cut_rule=("frac", 0.0, 0.0), target_source="uniform")
+    base = wl["h_teacher"][:1].clone()
+    wl["h_teacher"][:] = base + 0.125 * wl["h_teacher"]
+    cols = torch.arange(ties, device="cuda") * (V // ties) + V // ties - 1
+    wl["w_teacher"][:, cols] = 0.5 * base.t()   # logits near |base|^2 / 2, the rest near N(0, 1)
+    hip = run_hip(wl, narrow=narrow)
+    assert hip["stats"]["kernel"] == "mfma" and hip["stats"]["flagged"] >= T
+    np.testing.assert_array_equal(hip["am_t"], np.full(T, int(cols[0]), dtype=np.int32))
+    compare(hip, wl, label="ties-%d-%d" % (ties, T))
