@@ -4,8 +4,8 @@
 // order, gathers the realised token's logit of each model as a coalesced dot
 // product of the hidden row with the token's weight row, and writes
 //   logp_X = s_X z_X[y] - lse_X,   lse_X = s_X best_X + ln Z_X,
-//   kl     = A / Z_T - lse_T + lse_S   (KL(teacher || student), in-region only),
-//   kl_rev = B / Z_S - lse_S + lse_T   (KL(student || teacher), in-region only),
+//   kl     = A / Z_T - (lse_T - lse_S)   (KL(teacher || student), in-region only),
+//   kl_rev = B / Z_S + (lse_T - lse_S)   (KL(student || teacher), in-region only),
 //   argmax_X = lowest index attaining the max,
 // queueing rows whose top-2 gap is inside the fp32 error window for the exact
 // re-decision of their greedy token (on the MFMA path straight into its filter's queue).
@@ -249,18 +249,23 @@ combine_kernel(ScoreArgs a, int same_scale, const int32_t *__restrict__ targets,
         if (lse_out) lse_out[j * 2 + 1] = lse_t;
         if (logp_t) logp_t[g] = a.sT * zy_t - lse_t;
         if (am_t) am_t[g] = st.idx;
+        // lse_T - lse_S = dmax + dlnz: from the maxima's difference in 64 bits and the log of
+        // the sums' ratio, since the normalisers themselves carry roundings of their own
+        // magnitude (about 1e-6 at 10) into divergences near 1
+        const double dmax = (double)a.sT * st.best - (double)a.sS * ss.best;
+        const float dlnz = fast_log2(st.z / ss.z) * kLn2;
         if (kl) {
             // the teacher-weighted mean of the logit difference: A / Z_T, or with the
             // 256 x 256 kernel's fp16 weights A / (their sum)
             float an = same_scale ? a.sT * acc_a : acc_a;
-            float v = an / (zh_t ? acc_zh : st.z) - lse_t + lse_s;
+            float v = (float)((double)(an / (zh_t ? acc_zh : st.z)) - dmax) - dlnz;
             kl[g] = inr ? v : 0.f;
         }
         if (kl_rev) {
             // KL(student || teacher) = sum p_S (s_S zS - s_T zT) - lse_S + lse_T, or with
             // the 256 x 256 kernel's fp16 student weights B / (their sum)
             float bn = same_scale ? a.sS * acc_b : acc_b;
-            float v = bn / (zh_s ? acc_zh : ss.z) - lse_s + lse_t;
+            float v = (float)((double)(bn / (zh_s ? acc_zh : ss.z)) + dmax) + dlnz;
             kl_rev[g] = inr ? v : 0.f;
         }
     }
