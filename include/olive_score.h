@@ -90,7 +90,7 @@ typedef struct {
     int32_t flags;              /* bit set of OLIVE_FLAG_* (0 = defaults) */
 } olive_score_desc;
 
-/* Force the generic fp32-FMA kernel even where the bf16 MFMA kernel applies. The
+/* Force the generic kernel (fp32 products) even where the bf16 MFMA kernel applies. The
  * MFMA kernel applies to bf16 contexts whose hidden widths are multiples of 64, with
  * V >= 256 and 16-byte aligned weight and hidden-state buffers; every other case runs
  * the generic kernel, which returns the same outputs more slowly. */
