@@ -487,16 +487,21 @@ struct Kernel {
             }
     }
 
-    // The wavefront's largest squared norms into the call's, as norms with the margin the
-    // rounding bounds use (fp32 sums of d / 2 squares, the dot products' own rounding and
-    // the square root stay far inside 1e-4).
+    // The wavefront's largest squared norms into the call's, as upper bounds of the norms
+    // with the margin the rounding bounds use. A row's sum is formed in d / 2 dot products
+    // of two squares each, d / 4 chained per lane: at d = 12288 up to 4 roundings of 2^-24
+    // each make it at most 7.4e-4 short, the norm 3.7e-4, which the factor 1.0001 (1 + 2^-10)
+    // covers. Squares below the normal range vanish: up to 3 x 2^-126 a dot product (two
+    // products, one sum), d 2^-125 in all, which is added back (nothing to weights of any
+    // ordinary size; without it weights below 2^-63 had norm 0 and lost near ties).
     static __device__ __forceinline__ void publish_norms(const ScoreArgs &a,
                                                          const float (&wsq)[2], int lane) {
 #pragma unroll
         for (int m = 0; m < (HAS_T ? 2 : 1); ++m) {
             float x = wsq[m];
             for (int off = 16; off > 0; off >>= 1) x = fmaxf(x, __shfl_xor(x, off));
-            const float n = sqrtf(x) * (1.0001f * (1.0f + 0x1p-10f));
+            const float n = sqrtf(x + (float)(m ? a.dt : a.ds) * 0x1p-125f) *
+                            (1.0001f * (1.0f + 0x1p-10f));
             // norms are not negative: their bits order as they do
             if (lane == 0)
                 atomicMax((uint32_t *)const_cast<Sched *>(a.sched)->wmax + m, __float_as_uint(n));

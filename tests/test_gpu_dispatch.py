@@ -186,6 +186,66 @@ def test_static_call_forms_its_own_norms(T, V, scales, simple):
     compare({k: to_np(v) for k, v in o.items()}, wl, label="static-%d-%d" % (T, V))
 
 
+# Near ties that the weight norms decide: the exact winner's terms are B, s .. s, -B, so that
+# its fp32 logit loses the s beside B and falls below theta, the lower bound of the maximum
+# that the fp32 winner (all terms 0.75 s) sets with its own small rounding bound; only
+# delta = d 2^-23 |h| max |w| with the winner's own norm takes it in. The other columns stay
+# below both. The winner is the one row with a large norm, in the first, a middle or the
+# (shifted) last vocabulary tile, of one and of three position tiles; 2^-90 scales it to
+# where the squares of its weights underflow.
+def norm_pair(V, d, winner, rival, scale):
+    big, s = 2.0 ** 10, 2.0 ** -22
+    w = torch.full((V, d), -0.2 / d, dtype=torch.float64)
+    w[winner] = s
+    w[winner, 0], w[winner, -1] = big, -big
+    w[rival] = 0.75 * s
+    w = (w * scale).to(torch.bfloat16)
+    # the decision is the norm's: the winner's fp32 logit, in K order and in blocks of 16,
+    # lies below theta and below what the other rows' norms allow, not below the bound
+    z = w.double().sum(dim=1)
+    assert int(z.argmax()) == winner
+    norm = w.double().norm(dim=1)
+    other = torch.cat([norm[:winner], norm[winner + 1:]]).max()
+    slack = d * 2.0 ** -23
+    theta = float(z[rival] * (1 - slack))
+    x = w[winner].float()
+    for parts in (x, x.reshape(-1, 16).double().sum(dim=1)):
+        acc = np.float32(0)
+        for v in parts.tolist():
+            acc = np.float32(acc + v)
+        assert theta - slack * d ** 0.5 * float(norm[winner]) < acc < \
+            theta - slack * d ** 0.5 * float(other)
+    return w
+
+
+@pytest.mark.parametrize("kind", ["static", "static-generic", "context"])
+@pytest.mark.parametrize("T,ws,wt", [(1, 0, 2), (300, 1, 0), (300, 2, 1)])
+@pytest.mark.parametrize("exponent", [0, -90])
+def test_weight_norms_decide_near_ties(kind, T, ws, wt, exponent):
+    say("norms decide", kind, T, ws, wt, exponent)
+    V, ds, dt = 3001, 64, 192
+    winner = (5, 1500, 2999)   # the last tile holds rows 2745 .. 3000
+    w = [norm_pair(V, d, winner[k], r, 2.0 ** exponent).cuda()
+         for d, k, r in ((ds, ws, 700), (dt, wt, 2000))]
+    h = [torch.ones(T, d, dtype=torch.bfloat16, device="cuda") for d in (ds, dt)]
+    cu, cut, y = (torch.tensor(x, dtype=torch.int32, device="cuda") for x in ([0, T], [0], [0] * T))
+    batch = L.make_batch(cu, cut, y, h[0], h[1], None)
+    kl = torch.empty(T, device="cuda")
+    am = [torch.full((T,), -7, dtype=torch.int32, device="cuda") for _ in range(2)]
+    desc = L.make_desc(V, ds, dt, L.OLIVE_BF16, L.OLIVE_W_VD, 1.0, 1.0, max_positions=T, max_seqs=1,
+                       flags=L.OLIVE_FLAG_SIMPLE_KERNEL if kind == "static-generic" else 0)
+    if kind == "context":
+        ctx = L.olive_score_init(desc, w[0], w[1])
+        L.olive_kl_masked(ctx, batch, kl, None, None, None, am[0], am[1])
+        torch.cuda.synchronize()
+        L.olive_score_free(ctx)
+    else:
+        L.olive_kl_masked_static(desc, w[0], w[1], batch, kl, None, None, None, am[0], am[1])
+        torch.cuda.synchronize()
+    for m, k in ((0, ws), (1, wt)):
+        np.testing.assert_array_equal(to_np(am[m]), np.full(T, winner[k], dtype=np.int32))
+
+
 # Top-K lists of more splits than 32 (few position tiles, up to 64) and their selection.
 @pytest.mark.parametrize("T", [1, 100, 400])
 def test_topk_with_many_splits(T):
