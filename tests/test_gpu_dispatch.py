@@ -139,6 +139,37 @@ def test_generic_kernel_nan_and_infinite_rows_stay_their_own():
     np.testing.assert_array_equal(hip["logp_t"], clean["logp_t"])
 
 
+# Infinite logits of the generic kernel (rows 10 and 11 are one lane's, 200 another's): two of
+# +inf leave no normaliser, wherever they lie, one has all the weight; those of -inf have none.
+@pytest.mark.parametrize("rows", [(10,), (10, 11), (10, 200), (10, 11, 40, 299)])
+def test_generic_kernel_infinite_logits(rows):
+    say("generic kernel, infinite logits", rows)
+    V, d, T = 300, 33, 3
+    g = torch.Generator(device="cuda").manual_seed(3)
+    w = torch.randn(V, d, generator=g, device="cuda")
+    w[:, 0] = 0.0
+    h = torch.zeros(T, d, device="cuda")
+    h[:, 0], h[:, 1] = 1e20, 1.0
+    cu, cut, y = (torch.tensor(x, dtype=torch.int32, device="cuda")
+                  for x in ([0, T], [0], [0, 100, 298]))
+    desc = L.make_desc(V, d, 0, L.OLIVE_F32, L.OLIVE_W_VD, 1.0, max_positions=T, max_seqs=1)
+    for sign in (1.0, -1.0):
+        w[list(rows), 0] = sign * 1e30
+        logp = torch.zeros(T, device="cuda")
+        ctx = L.olive_score_init(desc, w)
+        L.olive_token_logprobs(ctx, L.make_batch(cu, cut, y, h), logp)
+        torch.cuda.synchronize()
+        L.olive_score_free(ctx)
+        if sign > 0:
+            want = -np.inf if len(rows) == 1 else np.nan
+            np.testing.assert_array_equal(to_np(logp), np.full(T, want, dtype=np.float32))
+        else:
+            z = to_np(w[:, 1]).astype(np.float64)
+            keep = np.setdiff1d(np.arange(V), rows)
+            np.testing.assert_allclose(to_np(logp), z[[0, 100, 298]] - np.logaddexp.reduce(z[keep]),
+                                       atol=1e-5)
+
+
 # The generic path's exact re-decision cuts its vocabulary chunks by the flagged rows'
 # count: 1 row, a batch and one more (8 parts a chunk), and enough for whole chunks.
 @pytest.mark.parametrize("dtype,ties", [("f32", 1), ("f32", 9), ("bf16", 9), ("f32", 400)])
