@@ -207,6 +207,9 @@ struct GemmArgs {
     int a_prows;
 };
 
+// Tiles of `tile` rows that hold `rows` rows (kOneChunk of them too: the sum needs 64 bits).
+constexpr int64_t tiles_of(int64_t rows, int tile) { return (rows + tile - 1) / tile; }
+
 // Floats one partial field holds: MAX_SPLITS splits of every row a call may have, or up to
 // MAX_SPLITS_FEW (one per 128 vocabulary rows at most) of few position tiles (tiles x
 // splits <= n_cu, 256 rows a tile at most).

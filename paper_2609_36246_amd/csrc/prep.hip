@@ -208,13 +208,13 @@ prep_kernel(const int32_t *__restrict__ cu, const int32_t *__restrict__ cut,
         if (pass_tile == 0) return;
         const int full = tid < 128 ? 1 : 0;
         const int rows = full ? pass_chunk : (int)(scored % pass_chunk);
-        const int s = pick_splits((rows + pass_tile - 1) / pass_tile, n_vtiles, grid, 1,
+        const int s = pick_splits((int)tiles_of(rows, pass_tile), n_vtiles, grid, 1,
                                   MAX_SPLITS_FEW, pass_tile, fstride);
         if ((tid & 63) == 0) sched->pass_splits[1 - full] = s;
         return;
     }
     const int t_valid = carry;   // compacted rows: valid, or in-region when region-only
-    const int n_p = (t_valid + tile_rows - 1) / tile_rows;
+    const int n_p = (int)tiles_of(t_valid, tile_rows);
     const int ns = pick_splits(n_p, n_vtiles, grid, min_splits, max_splits, tile_rows, fstride,
                                min_splits > 1);
     if (tid == 0) {
