@@ -122,6 +122,8 @@ filter_kernel(ScoreArgs a, FilterQueue w) {
                 if (v < a.V && acc[cb][r] >= thr) {
                     const int n = atomicAdd(&w.qcnt[m * w.cap + q], 1);
                     if (n < w.ccap) w.cand[((int64_t)m * w.cap + q) * w.ccap + n] = v;
+                    // the first one too many lists the pair for the exhaustive scan
+                    if (n == w.ccap) w.fb[atomicAdd(w.nfb, 1)] = m * w.cap + q;
                 }
             }
         }

@@ -56,6 +56,8 @@ __device__ __forceinline__ void fx_queue_pair(const ScoreArgs &a, const FilterQu
         q.qj[m * q.cap + slot] = (int32_t)j;
         q.qthr[m * q.cap + slot] = thr;
         q.qcnt[m * q.cap + slot] = cnt;
+        // (a pair that is still to overflow is listed by the filter)
+        if (cnt > q.ccap) q.fb[atomicAdd(q.nfb, 1)] = m * q.cap + slot;
     }
 }
 

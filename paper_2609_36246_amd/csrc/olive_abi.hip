@@ -624,7 +624,7 @@ bool static_carve(olive_score_ctx *c, char *base) {
     c->wn_t = (float *)take((size_t)kStaticMaxVocab * sizeof(float));
     if (off > kStaticScratchBytes) return false;
     c->fxq = filter_queue_carve(c->fx_buf, c->flag_cap, FX_CCAP, &c->sched->n_fxq[0],
-                                nullptr);
+                                &c->sched->n_fx_fb);
     c->fxq.smask = &c->sched->fx_smask[0][0];
     return true;
 }
@@ -759,7 +759,7 @@ olive_status olive_score_init(olive_score_ctx **out, const olive_score_desc *des
         s = dev_alloc(&c->fx_buf, filter_queue_bytes(c->flag_cap, FX_CCAP));
         if (!s) {
             c->fxq = filter_queue_carve(c->fx_buf, c->flag_cap, FX_CCAP, &c->sched->n_fxq[0],
-                                        nullptr);
+                                        &c->sched->n_fx_fb);
             c->fxq.smask = &c->sched->fx_smask[0][0];   // the greedy filter reads marked splits
         }
     }

@@ -48,7 +48,7 @@ constexpr int FX_CCAP = 64;  // candidates kept per near-tie pair of the greedy 
 // candidates (launch_filter). Carved from one allocation (filter_queue_carve).
 struct FilterQueue {
     int32_t *n;          // device [2]: queued pairs per model (Sched fields)
-    int32_t *nfb;        // device: pairs sent to the exhaustive scan (a Sched field; top-K)
+    int32_t *nfb;        // device: pairs listed for the exhaustive scan (a Sched field)
     int32_t *qj;         // [2][cap] compacted row
     float *qthr;         // [2][cap] fp32 threshold on the raw logit h . w
     int32_t *qcnt;       // [2][cap] candidates found (may exceed ccap)
@@ -100,6 +100,7 @@ struct alignas(16) Sched {
     int32_t n_tkq[2];   // (row, model) pairs whose top-K field needs the vocabulary filter
     int32_t n_tk_fb;    // pairs of those that need the exhaustive exact scan
     int32_t n_fxq[2];   // near-tie (row, model) pairs of the greedy re-decision (MFMA path)
+    int32_t n_fx_fb;    // pairs of those that need the exhaustive exact scan
     uint32_t fx_smask[2][SPLIT_WORDS];   // per model: vocabulary splits (bit s % 32 of word
                                          // s / 32) the re-decision's filter must read
 };

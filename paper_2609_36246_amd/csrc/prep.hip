@@ -126,7 +126,7 @@ prep_kernel(const int32_t *__restrict__ cu, const int32_t *__restrict__ cut,
             sched->n_scored = 0; sched->n_flagged = 0; sched->cu_bad = 1;
             sched->fl_models = 0u; sched->wmax[0] = 0.f; sched->wmax[1] = 0.f;
             sched->n_tkq[0] = 0; sched->n_tkq[1] = 0; sched->n_tk_fb = 0;
-            sched->n_fxq[0] = 0; sched->n_fxq[1] = 0;
+            sched->n_fxq[0] = 0; sched->n_fxq[1] = 0; sched->n_fx_fb = 0;
             sched->pstride = 0;
             sched->pass_splits[0] = 1; sched->pass_splits[1] = 1;
             for (int w = 0; w < 2 * SPLIT_WORDS; ++w) sched->fx_smask[0][w] = 0u;
@@ -228,7 +228,7 @@ prep_kernel(const int32_t *__restrict__ cu, const int32_t *__restrict__ cut,
         sched->n_flagged = 0;
         sched->fl_models = 0u; sched->wmax[0] = 0.f; sched->wmax[1] = 0.f;
         sched->n_tkq[0] = 0; sched->n_tkq[1] = 0; sched->n_tk_fb = 0;
-        sched->n_fxq[0] = 0; sched->n_fxq[1] = 0;
+        sched->n_fxq[0] = 0; sched->n_fxq[1] = 0; sched->n_fx_fb = 0;
         sched->pstride = n_p * tile_rows;
         for (int w = 0; w < 2 * SPLIT_WORDS; ++w) sched->fx_smask[0][w] = 0u;
         sched->cu_bad = 0;

@@ -161,7 +161,7 @@ topk_select_kernel(ScoreArgs a, TopkWork w) {
 }
 
 // One wavefront per queued pair: exact values of its kept indices, ranked. A pair
-// with more indices than were kept goes to the exhaustive scan.
+// with more indices than were kept is the exhaustive scan's (the filter listed it).
 __global__ void __launch_bounds__(256)
 topk_exact_kernel(ScoreArgs a, TopkWork w) {
     __shared__ double cx[4][TK_CAP];
@@ -179,10 +179,7 @@ topk_exact_kernel(ScoreArgs a, TopkWork w) {
         const int q = (int)(m ? p - nq[0] : p);
         const int n = f.qcnt[m * f.cap + q];
         const int64_t j = f.qj[m * f.cap + q];
-        if (n > f.ccap) {
-            if (lane == 0) f.fb[atomicAdd(f.nfb, 1)] = m * f.cap + q;
-            continue;
-        }
+        if (n > f.ccap) continue;
         const int d = m ? a.dt : a.ds;
         const int64_t g = a.rowmap[j] & 0x7fffffffu;
         const uint16_t *h = (const uint16_t *)(m ? a.ht : a.hs) + g * d;

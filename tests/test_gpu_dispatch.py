@@ -297,8 +297,8 @@ def test_topk_with_many_splits(T):
 
 
 # The greedy re-decision on the MFMA path: exact ties of the teacher's winner with up to 64
-# candidates (decided from the queue), with more (the exhaustive scan, by the workgroup that
-# finds the overflow), on rows that fill a workgroup's four wavefronts, fewer and more.
+# candidates (decided from the queue), with more (the exhaustive scan, a workgroup each), on
+# rows that fill a workgroup's four wavefronts, fewer and more.
 @pytest.mark.parametrize("ties,T", [(2, 1), (3, 9), (64, 5), (65, 1), (300, 3), (300, 9)])
 @pytest.mark.parametrize("narrow", [False, True], ids=["wide", "narrow"])
 def test_greedy_ties_beyond_the_queue(ties, T, narrow):
@@ -314,3 +314,37 @@ def test_greedy_ties_beyond_the_queue(ties, T, narrow):
     assert hip["stats"]["kernel"] == "mfma" and hip["stats"]["flagged"] >= T
     np.testing.assert_array_equal(hip["am_t"], np.full(T, int(cols[0]), dtype=np.int32))
     compare(hip, wl, label="ties-%d-%d" % (ties, T))
+
+
+# Exhaustive scans of several pairs run side by side: 8 rows with 300 tied columns each take
+# about as long as one (a scan is all of such a call's time: 6.4 ms here; in turn on two
+# compute units they took 24 ms).
+def test_exhaustive_scans_run_side_by_side():
+    say("exhaustive scans side by side")
+    V, T = 32000, 64
+    took = {}
+    for rows in (1, 8):
+        wl = custom("scans", num_seqs=1, seq_len=T, vocab=V, d_student=64, d_teacher=1024,
+                    cut_rule=("frac", 0.0, 0.0), target_source="uniform")
+        h = wl["h_teacher"].float()
+        base = h[0] / h[0].norm()
+        h -= (h @ base)[:, None] * base + 2.0 * base    # -2 along base, the tied rows +32
+        h[:rows] += 34.0 * base
+        wl["h_teacher"].copy_(h.to(torch.bfloat16))
+        cols = torch.arange(300, device="cuda") * (V // 300) + 7
+        wl["w_teacher"][:, cols] = (0.5 * base).to(torch.bfloat16)[:, None]
+        hip = run_hip(wl, keep_ctx=True)
+        np.testing.assert_array_equal(hip["am_t"][:rows], np.full(rows, 7, dtype=np.int32))
+        assert rows <= hip["stats"]["flagged"] <= rows + 4
+        best = []
+        for _ in range(5):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            run_hip(wl, ctx=hip["ctx"], outputs=("logp_s", "am_t"))
+            b.record()
+            b.synchronize()
+            best.append(a.elapsed_time(b))
+        took[rows] = min(best)
+        L.olive_score_free(hip["ctx"])
+    say("one scan %.2f ms, eight %.2f ms" % (took[1], took[8]))
+    assert took[8] < 2.0 * took[1], took
