@@ -351,8 +351,8 @@ olive_status olive_score_backward(olive_score_ctx *ctx, const olive_batch *b,
  * (several streams or host threads) race and must not be issued. The device error word
  * is not reported: content errors make the affected outputs NaN as in olive_kl_masked.
  * The weight-row norms that bound the rounding of the exact greedy decisions are formed by
- * the call itself: by the scoring pass on the MFMA path, by one more read of a model's
- * weights where the generic kernel flags a row of that model.
+ * the call itself where it has greedy outputs: by the scoring pass on the MFMA path, by one
+ * more read of a model's weights where the generic kernel flags a row of that model.
  * Errors: E_NULL, E_DTYPE, E_SHAPE, E_RANGE, E_UNSUPPORTED, E_LIMIT, E_HIP, and the
  * checks of olive_kl_masked on the batch.
  */

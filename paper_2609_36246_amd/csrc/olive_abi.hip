@@ -272,13 +272,15 @@ olive_status run(olive_score_ctx *ctx, const olive_batch *b, const olive_spans *
         s = check_hip(launch_panel_h(a, st));
         if (s) return s;
     }
+    const bool flagging = am_s || (has_t && am_t);   // near ties are decided exactly
     const int slot = (int)(ctx->n_calls % 64);
     if (ctx->timing && hipEventRecord(ctx->ev[0][slot], st) != hipSuccess) return OLIVE_E_HIP;
     if (wide)
         s = check_hip(launch_score_wide(a, same_scale, has_t, wide_rev, grid, st));
     else if (mfma)
+        // (the norms bound the near ties' roundings: without greedy outputs nobody asks)
         s = check_hip(launch_score_mfma(a, has_t, same_scale, has_t && kl_rev, topk,
-                                        ctx->no_init, grid, st));
+                                        ctx->no_init && flagging, grid, st));
     else
         s = check_hip(launch_score_simple(a, ctx->bf16, has_t, grid, st));
     if (s) return s;
@@ -288,7 +290,6 @@ olive_status run(olive_score_ctx *ctx, const olive_batch *b, const olive_spans *
     ctx->last_grid = grid;
 
     // near ties: the generic path lists the rows, the MFMA path queues them
-    const bool flagging = am_s || (has_t && am_t);
     int32_t *flagged = flagging && !mfma ? ctx->flagged : nullptr;
     const FilterQueue fq = flagging && mfma ? ctx->fxq : FilterQueue{};
     s = check_hip(launch_combine(a, ctx->bf16, has_t, same_scale, b->targets, ctx->err, logp_s,
