@@ -185,18 +185,10 @@ __device__ __forceinline__ int dev_count(const int32_t *p, int off, int cap, int
     return n < cap ? n : cap;
 }
 
-// Parts of K per tile: the count up to 64 that costs least on G workgroups, in eighths of
-// a K step: rounds of the grid x (a part's steps + 6 for a unit's start and end), and one
-// for each partial tile written and added (512 KB moved). Up to `room` partial tiles fit
-// the workspace; every part has a step. Called by whole wavefronts: lane l tries l + 1.
+// Parts of K per tile (gemm_split_key). Called by whole wavefronts: lane l tries l + 1.
 __device__ __forceinline__ int gemm_splits(uint32_t n_tiles, int ksteps, int G, int64_t room) {
-    const int S = (int)(threadIdx.x & 63) + 1;
-    const int per = (ksteps + S - 1) / S;
-    uint64_t key = ~0ull;
-    if (S == 1 || ((int64_t)(S - 1) * n_tiles <= room && (S - 1) * per < ksteps)) {
-        const uint64_t rounds = ((uint64_t)n_tiles * S + G - 1) / (uint64_t)G;
-        key = ((rounds * (uint64_t)(per + 6) * 8 + (uint64_t)(S - 1) * n_tiles) << 7) | (uint64_t)S;
-    }
+    static_assert(GEMM_PARTS == 64, "a lane per count");
+    uint64_t key = gemm_split_key((int)(threadIdx.x & 63) + 1, n_tiles, ksteps, G, room);
     for (int off = 32; off > 0; off >>= 1) {
         const uint64_t o = __shfl_xor(key, off);
         key = o < key ? o : key;

@@ -776,13 +776,8 @@ olive_status olive_score_init(olive_score_ctx **out, const olive_score_desc *des
         if (!s)
             s = dev_alloc(&c->bw_mref,
                           ((size_t)(V + 255) / 256 + 2) * c->bw_chunk * sizeof(float));
-        // a second part of every tile of a chunk's dL/dh product, and with few tiles as many
-        // parts as three rounds of the grid hold beside the first (5941 rows at d_S = 2048,
-        // 192 tiles on 256 compute units: 4 parts; with room for two rounds one part, 3.38 ms
-        // of a backward of 10.40, which takes 10.04 now)
-        const int64_t tiles = (ds + GEMM_TILE - 1) / GEMM_TILE *
-                              ((c->bw_chunk + GEMM_TILE - 1) / GEMM_TILE);
-        c->bw_gtiles = tiles > 3 * c->n_cu ? tiles : 3 * c->n_cu;
+        c->bw_gtiles = gemm_ws_tiles(tiles_of(ds, GEMM_TILE) * tiles_of(c->bw_chunk, GEMM_TILE),
+                                     c->bw_vp / 64, c->n_cu);   // of the dL/dh product
         if (!s)
             s = dev_alloc(&c->bw_gws,
                           (size_t)c->bw_gtiles * GEMM_TILE * GEMM_TILE * sizeof(float));

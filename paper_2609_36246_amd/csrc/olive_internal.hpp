@@ -222,6 +222,30 @@ inline int64_t part_field_floats(int64_t max_positions, int64_t vocab, int n_cu)
     return all > few ? all : few;
 }
 
+// K parts per tile of a product split over more units: cost of S parts on G workgroups, in
+// eighths of a K step, above S itself (the smallest key is chosen): rounds of the grid x (a
+// part's steps + 6 for a unit's start and end), and one for each partial tile written and
+// added (512 KB moved). Up to `room` partial tiles fit the workspace; every part has a step.
+constexpr int GEMM_PARTS = 64;
+constexpr uint64_t gemm_split_key(int S, uint32_t n_tiles, int ksteps, int G, int64_t room) {
+    const int per = (ksteps + S - 1) / S;
+    if (S > 1 && ((int64_t)(S - 1) * n_tiles > room || (int64_t)(S - 1) * per >= ksteps))
+        return ~(uint64_t)0;
+    const uint64_t rounds = ((uint64_t)n_tiles * S + G - 1) / (uint64_t)G;
+    return ((rounds * (uint64_t)(per + 6) * 8 + (uint64_t)(S - 1) * n_tiles) << 7) | (uint64_t)S;
+}
+
+// Partial tiles kept for a product of up to `tiles` tiles and `ksteps` K steps: a second part
+// of every tile, and with few tiles as many parts as three rounds of the grid hold beside the
+// first (5941 rows at d_S = 2048, 192 tiles on 256 compute units: 4 parts; with room for two
+// rounds one part, 3.38 ms of a backward of 10.40, which takes 10.04 now), but no more than
+// the most parts use (a context of 64 rows, V = 1000, d_S = 64: 15 instead of 768, 201 MB).
+constexpr int64_t gemm_ws_tiles(int64_t tiles, int64_t ksteps, int n_cu) {
+    const int64_t parts = ksteps < GEMM_PARTS ? ksteps : GEMM_PARTS;
+    const int64_t used = (parts - 1) * tiles, most = tiles > 3 * n_cu ? tiles : 3 * n_cu;
+    return used < most ? used : most;
+}
+
 // Host-side launchers (each defined beside its kernel).
 hipError_t launch_filter(const ScoreArgs &a, const FilterQueue &q, hipStream_t st);
 hipError_t launch_repack(const void *w_dv, void *w_vd, int64_t d, int64_t V, int elem_bytes,

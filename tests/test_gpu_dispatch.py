@@ -101,6 +101,23 @@ def test_backward_product_splits(T, ds, V):
     check_grads(hip, oracle_backward(wl, 1.0, 0.0, O.REGION_TEACHER), wl, "product-%d" % T)
 
 
+# The workspace of the dL/dh product is no larger than its splits use.
+def test_small_backward_context_is_small():
+    say("memory of a small backward context")
+    wl = custom("small-bw", num_seqs=1, seq_len=64, vocab=1000, d_student=64, d_teacher=64,
+                cut_rule=("frac", 0.0, 0.0))
+    run_backward(wl)   # the library's code and the runtime's own memory are loaded
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    ctx = L.olive_score_init(
+        L.make_desc(1000, 64, 64, L.OLIVE_BF16, L.OLIVE_W_DV, max_positions=64, max_seqs=1,
+                    flags=L.OLIVE_FLAG_BACKWARD), wl["w_student"], wl["w_teacher"])
+    used = before - torch.cuda.mem_get_info()[0]
+    L.olive_score_free(ctx)
+    say("%.1f MB" % (used / 1e6))
+    assert used < 64e6, used
+
+
 # The generic kernel's tiles: 128 vocabulary rows x 64 positions, K in steps of 32 read in
 # groups of 4 elements where width and alignment allow; edges and remainders of each.
 @pytest.mark.parametrize("dtype,T,V,ds,dt,off", [
