@@ -106,10 +106,12 @@ typedef struct {
 /* Reserve the workspace of olive_score_backward. Needs a bf16 context on which the
  * MFMA kernel applies (else init returns E_UNSUPPORTED). The workspace holds about
  * 2 (V + d_S) R + 2 d_S V + 8 max_positions + 4 (V / 256 + 2) R bytes of device memory,
- * R = min(max_positions, 8192), plus 256 KiB for each of
- * min(max(t, 3 compute units), (min(64, V / 64) - 1) t) partial tiles of the dL/dh product,
- * t = (d_S / 256) (R / 256) rounded up each (3.4 GB for V = 151936, d_S = 2048 and 8192 or
- * more positions, 0.2 GB of it the partial tiles; 6 MB for V = 1000, d_S = 64 and 64). */
+ * R = min(max_positions, 8192), plus 256 KiB for each partial tile of the products:
+ * min(max(t, 3 c), (min(64, V / 64) - 1) t) of dL/dh, t = (d_S / 256) (R / 256) rounded up
+ * each, on c compute units, or if more min(3 c, (min(64, R / 64) - 1) u) of dL/dW where its
+ * u = (d_S / 256) (V / 256) tiles are at most c / 2 (3.4 GB for V = 151936, d_S = 2048 and
+ * 8192 or more positions, 0.2 GB of it the partial tiles; 6 MB for V = 1000, d_S = 64 and
+ * 64 positions). */
 #define OLIVE_FLAG_BACKWARD 8
 /* Score with the 256 x 128 two-model MFMA kernel instead of the 256 x 256 one. Without
  * this flag a bf16 context on which the MFMA kernel applies keeps K-blocked copies of its

@@ -522,6 +522,12 @@ olive_status run_backward(olive_score_ctx *ctx, const olive_batch *b, const oliv
             g.ldc = dv ? V : ds;
             g.alpha = a.sS;
             g.accumulate = c0 > 0;
+            // few tiles of V / 256 x d_S / 256 leave the grid idle over all the chunk's rows
+            if (gemm_may_split(tiles_of(V, GEMM_TILE) * tiles_of(ds, GEMM_TILE),
+                               tiles_of(T - c0 < ch ? T - c0 : ch, 64), grid, true)) {
+                g.ws = ctx->bw_gws;
+                g.ws_tiles = ctx->bw_gtiles;
+            }
             s = check_hip(launch_gemm(g, grid, st));
             if (s) return s;
         }
@@ -538,7 +544,7 @@ olive_status run_backward(olive_score_ctx *ctx, const olive_batch *b, const oliv
             g.K = (int)ctx->bw_vp;
             g.n_dev = &ctx->sched->t_valid;
             g.n_off = (int)c0;
-            g.n_cap = ch;
+            g.n_cap = (int)(T - c0 < ch ? T - c0 : ch);
             g.C = go->grad_h_student;               // row of scored row n: rowmap[c0 + n]
             g.ldc = ds;
             g.rowmap = ctx->rowmap;
@@ -547,8 +553,12 @@ olive_status run_backward(olive_score_ctx *ctx, const olive_batch *b, const oliv
             g.alpha = a.sS;
             g.accumulate = false;
             // d_S / 256 x rows / 256 tiles rarely fill the grid: K is split
-            g.ws = ctx->bw_gws;
-            g.ws_tiles = ctx->bw_gtiles;
+            if (gemm_may_split(tiles_of(ds, GEMM_TILE) *
+                                   tiles_of(T - c0 < ch ? T - c0 : ch, GEMM_TILE),
+                               ctx->bw_vp / 64, grid, false)) {
+                g.ws = ctx->bw_gws;
+                g.ws_tiles = ctx->bw_gtiles;
+            }
             s = check_hip(launch_gemm(g, grid, st));
             if (s) return s;
         }
@@ -776,8 +786,15 @@ olive_status olive_score_init(olive_score_ctx **out, const olive_score_desc *des
         if (!s)
             s = dev_alloc(&c->bw_mref,
                           ((size_t)(V + 255) / 256 + 2) * c->bw_chunk * sizeof(float));
+        // partial tiles of the dL/dh product, or of a dL/dW one with few tiles
         c->bw_gtiles = gemm_ws_tiles(tiles_of(ds, GEMM_TILE) * tiles_of(c->bw_chunk, GEMM_TILE),
-                                     c->bw_vp / 64, c->n_cu);   // of the dL/dh product
+                                     c->bw_vp / 64, c->n_cu);
+        const int64_t wtiles = tiles_of(ds, GEMM_TILE) * tiles_of(V, GEMM_TILE);
+        const int64_t wsteps = tiles_of(c->bw_chunk, 64);
+        if (gemm_may_split(wtiles, wsteps, c->n_cu, true)) {
+            const int64_t w = gemm_ws_tiles(wtiles, wsteps, c->n_cu);
+            c->bw_gtiles = w > c->bw_gtiles ? w : c->bw_gtiles;
+        }
         if (!s)
             s = dev_alloc(&c->bw_gws,
                           (size_t)c->bw_gtiles * GEMM_TILE * GEMM_TILE * sizeof(float));

@@ -224,15 +224,29 @@ inline int64_t part_field_floats(int64_t max_positions, int64_t vocab, int n_cu)
 
 // K parts per tile of a product split over more units: cost of S parts on G workgroups, in
 // eighths of a K step, above S itself (the smallest key is chosen): rounds of the grid x (a
-// part's steps + 6 for a unit's start and end), and one for each partial tile written and
-// added (512 KB moved). Up to `room` partial tiles fit the workspace; every part has a step.
+// part's steps + 6 for a unit's start and end), one for each partial tile written and added
+// (512 KB moved), and a step for the kernel that adds them. Up to `room` partial tiles fit
+// the workspace; every part has a step.
 constexpr int GEMM_PARTS = 64;
 constexpr uint64_t gemm_split_key(int S, uint32_t n_tiles, int ksteps, int G, int64_t room) {
     const int per = (ksteps + S - 1) / S;
     if (S > 1 && ((int64_t)(S - 1) * n_tiles > room || (int64_t)(S - 1) * per >= ksteps))
         return ~(uint64_t)0;
     const uint64_t rounds = ((uint64_t)n_tiles * S + G - 1) / (uint64_t)G;
-    return ((rounds * (uint64_t)(per + 6) * 8 + (uint64_t)(S - 1) * n_tiles) << 7) | (uint64_t)S;
+    const uint64_t add = S > 1 ? (uint64_t)(S - 1) * n_tiles + 8 : 0;
+    return ((rounds * (uint64_t)(per + 6) * 8 + add) << 7) | (uint64_t)S;
+}
+
+// Whether a product of up to `tiles` tiles and `ksteps` K steps may be split at all: where
+// not, the launch that adds the parts (4 us, a K step takes 1.1) is saved. Not for one round
+// of the grid with few K steps (32 rows, V = 300, d_S = 64: dL/dh's 5 steps 9.8 us, in 5
+// parts 12.3 + 3.9), and not for dL/dW (known: its `tiles` are exact) from half the grid on,
+// where its at most 128 steps leave little to gain. With few tiles they ran on as many
+// compute units: 9000 rows, V = 600, d_S = 64, 3 tiles: 195 us of the 345 of a backward,
+// which takes 201.
+constexpr bool gemm_may_split(int64_t tiles, int64_t ksteps, int G, bool known) {
+    if (tiles <= G && ksteps <= 5) return false;
+    return !known || 2 * tiles <= G;
 }
 
 // Partial tiles kept for a product of up to `tiles` tiles and `ksteps` K steps: a second part

@@ -83,22 +83,55 @@ def test_backward_of_few_rows_many_splits():
         assert np.all(np.abs(to_np(gw) - ref["grad_w"]) <= bw)
 
 
-# The dL/dh product splits K over more units where its tiles (256 of d_S x 128 rows) leave
-# compute units idle: one tile with few K steps (a part per step), ragged tiles in both
-# directions, a reduced tile count that fits no second part evenly, and two chunks of rows
-# (the second one short). The parts add in a fixed order: repeated calls are bit-identical.
+# The products (tiles of 256 x 256) split K over more units where their tiles leave compute
+# units idle: dL/dh of one tile with few K steps (none) and more (up to a part per step),
+# ragged tiles in both directions, a tile count that fits no second part evenly, two chunks of
+# rows (the second one short); dL/dW of one and of several tiles, both layouts, an odd V, on
+# a second chunk, and one K step (no part). The parts add in a fixed order: repeated calls
+# are bit-identical.
 @pytest.mark.parametrize("T,ds,V", [(1, 64, 300), (129, 320, 20000), (700, 576, 3000),
-                                    (2900, 64, 1000), (8200, 128, 300)])
-def test_backward_product_splits(T, ds, V):
-    say("backward product", T, ds, V)
+                                    (2900, 64, 1000), (8200, 128, 300), (5000, 64, 257),
+                                    (8900, 320, 1001), (60, 64, 4000)])
+@pytest.mark.parametrize("layout", [L.OLIVE_W_DV, L.OLIVE_W_VD], ids=["dv", "vd"])
+def test_backward_product_splits(T, ds, V, layout):
+    say("backward product", T, ds, V, layout)
     wl = custom("parts", num_seqs=1, seq_len=T, vocab=V, d_student=ds, d_teacher=64,
                 cut_rule=("frac", 0.0, 0.0))
-    hip = run_backward(wl, keep_ctx=True)
-    again = run_backward(wl, ctx=hip["ctx"])
-    L.olive_score_free(hip["ctx"])
-    for k in ("h", "w"):
-        np.testing.assert_array_equal(hip[k], again[k], err_msg=k)
+    dv = layout == L.OLIVE_W_DV   # (run_backward drops the [V][d] weights a context borrows)
+    hip = run_backward(wl, keep_ctx=dv, layout=layout)
+    if dv:
+        again = run_backward(wl, ctx=hip["ctx"])
+        L.olive_score_free(hip["ctx"])
+        for k in ("h", "w"):
+            np.testing.assert_array_equal(hip[k], again[k], err_msg=k)
     check_grads(hip, oracle_backward(wl, 1.0, 0.0, O.REGION_TEACHER), wl, "product-%d" % T)
+
+
+# dL/dW of few tiles (three here) runs on as many compute units as dL/dh: over 9000 rows the
+# two gradients alone take about as long (145 and 130 us; 282 with dL/dW on three).
+def test_backward_products_of_few_tiles_fill_the_chip():
+    say("backward products of few tiles")
+    wl = custom("fewtiles", num_seqs=1, seq_len=9000, vocab=600, d_student=64, d_teacher=64,
+                cut_rule=("frac", 0.0, 0.0))
+    ctx = run_backward(wl, keep_ctx=True)["ctx"]
+    batch = L.make_batch(wl["cu_seqlens"], wl["cut"], wl["targets"], wl["h_student"],
+                         wl["h_teacher"], wl["valid_len"])
+    gh, gw = torch.empty(9000, 64, device="cuda"), torch.empty(64, 600, device="cuda")
+    grads = {"h": L.make_grad_outputs(1.0, 0.0, gh, None),
+             "w": L.make_grad_outputs(1.0, 0.0, None, gw)}
+    best = dict.fromkeys(grads, 1e9)
+    for _ in range(10):
+        for k, g in grads.items():
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            for _ in range(10):
+                L.olive_score_backward(ctx, batch, g)
+            b.record()
+            b.synchronize()
+            best[k] = min(best[k], a.elapsed_time(b) * 100.0)
+    L.olive_score_free(ctx)
+    say("dL/dh alone %.0f us, dL/dW alone %.0f us" % (best["h"], best["w"]))
+    assert best["w"] < 1.4 * best["h"], best
 
 
 # The workspace of the dL/dh product is no larger than its splits use.
