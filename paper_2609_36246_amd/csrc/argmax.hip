@@ -30,6 +30,12 @@ fx_exact_kernel(ScoreArgs a, FilterQueue q, int32_t *__restrict__ am_s,
     extern __shared__ __attribute__((aligned(16))) uint16_t fx_h[];   // [d] bf16
     __shared__ double red_v[SCAN_GROUPS][TOPK_K];
     __shared__ int red_i[SCAN_GROUPS][TOPK_K];
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    int nq[2];
+    for (int m = 0; m < 2; ++m) {
+        const int n = q.n[m];
+        nq[m] = n < q.cap ? n : q.cap;
+    }
     const int nfb = *q.nfb;
     for (int e = blockIdx.x; e < nfb; e += gridDim.x) {
         const int code = q.fb[e];
@@ -42,12 +48,6 @@ fx_exact_kernel(ScoreArgs a, FilterQueue q, int32_t *__restrict__ am_s,
         scan_row_top16((const uint16_t *)(m ? a.ht : a.hs) + g * d,
                        (const uint16_t *)(m ? a.wt : a.ws), d, a.V, fx_h, red_v, red_i, bv, bi);
         if (threadIdx.x == 0) (m ? am_t : am_s)[g] = bi;
-    }
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    int nq[2];
-    for (int m = 0; m < 2; ++m) {
-        const int n = q.n[m];
-        nq[m] = n < q.cap ? n : q.cap;
     }
     for (int64_t p = (int64_t)blockIdx.x * 4 + wid; p < nq[0] + nq[1];
          p += (int64_t)gridDim.x * 4) {
