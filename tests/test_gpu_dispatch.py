@@ -55,6 +55,21 @@ def test_few_positions_many_splits(T, outs, narrow):
     compare(hip, wl, student_only=outs == "student", label="few-%d-%s" % (T, outs))
 
 
+# The combine pass holds fewer registers from 4097 positions on, up to widths of 2048.
+@pytest.mark.parametrize("T,ds,dt", [(4096, 64, 128), (4097, 64, 128), (4097, 128, 2112)])
+@pytest.mark.parametrize("student", [False, True], ids=["both", "student"])
+def test_combine_of_many_positions(T, ds, dt, student):
+    say("combine", T, ds, dt, student)
+    wl = custom("combine", num_seqs=1, seq_len=T, vocab=300, d_student=ds, d_teacher=dt,
+                cut_rule=("frac", 0.2, 0.8), target_source="uniform")
+    z = wl["h_student"][T - 1].float() @ wl["w_student"].float()
+    j = int(torch.argmax(z))
+    wl["w_student"][:, 299] = wl["w_student"][:, j]   # the last row ties exactly
+    hip = run_hip(wl, student_only=student, outputs=("logp_s", "am_s") if student else FORWARD)
+    assert hip["stats"]["flagged"] >= 1 and hip["am_s"][T - 1] == min(j, 299)
+    compare(hip, wl, student_only=student, label="combine-%d-%d" % (T, dt))
+
+
 def test_backward_of_few_rows_many_splits():
     say("backward of few rows")
     wl = custom("fewbw", num_seqs=2, seq_len=100, vocab=33000, d_student=128, d_teacher=64,
