@@ -122,7 +122,11 @@ __device__ __forceinline__ void merge_lane(GRun &R, int off, float c) {
 
 }  // namespace
 
-template <typename E, bool HAS_T, bool VEC>
+// NG: groups of 8 K elements of a step that hold any, 4, or 1 for widths up to 8 (4096 positions
+// at V = 32000, d = 1: 379 us with the other three groups' MFMAs, over zeros, 290 without; 310
+// with one vocabulary row per thread. A last step cut short at run time instead cost every
+// width 15 %: 60 registers spilled).
+template <typename E, bool HAS_T, bool VEC, int NG>
 __global__ void __launch_bounds__(256, 2)
 score_simple_kernel(ScoreArgs a, int same_scale) {
     __shared__ __attribute__((aligned(16))) float stage[2][S_STAGE];
@@ -207,10 +211,10 @@ score_simple_kernel(ScoreArgs a, int same_scale) {
             float4 A = *(const float4 *)(sa + get_off[0]), B0 = *(const float4 *)(sb + get_off[0]),
                    B1 = *(const float4 *)(sb + 32 * SK + get_off[0]);
 #pragma unroll
-            for (int q = 0; q < SK / 8; ++q) {
+            for (int q = 0; q < NG; ++q) {
                 const float av[4] = {A.x, A.y, A.z, A.w}, b0[4] = {B0.x, B0.y, B0.z, B0.w},
                             b1[4] = {B1.x, B1.y, B1.z, B1.w};
-                if (q + 1 < SK / 8) {
+                if (q + 1 < NG) {
                     A = *(const float4 *)(sa + get_off[q + 1]);
                     B0 = *(const float4 *)(sb + get_off[q + 1]);
                     B1 = *(const float4 *)(sb + 32 * SK + get_off[q + 1]);
@@ -329,8 +333,10 @@ hipError_t launch_score_simple(const ScoreArgs &a, bool bf16, bool has_t, int gr
                                  (((uintptr_t)a.ht | (uintptr_t)a.wt) & mask) == 0));
 #define OLIVE_SIMPLE(E_, T_)                                                          \
     do {                                                                              \
-        if (vec) score_simple_kernel<E_, T_, true><<<grid, 256, 0, st>>>(a, same);    \
-        else score_simple_kernel<E_, T_, false><<<grid, 256, 0, st>>>(a, same);       \
+        if (a.ds <= 8 && a.dt <= 8)                                                   \
+            score_simple_kernel<E_, T_, false, 1><<<grid, 256, 0, st>>>(a, same);     \
+        else if (vec) score_simple_kernel<E_, T_, true, 4><<<grid, 256, 0, st>>>(a, same); \
+        else score_simple_kernel<E_, T_, false, 4><<<grid, 256, 0, st>>>(a, same);    \
     } while (0)
     if (bf16) {
         if (has_t) OLIVE_SIMPLE(uint16_t, true);

@@ -189,6 +189,21 @@ def test_generic_kernel_tile_edges(dtype, T, V, ds, dt, off):
     compare(alone, wl, student_only=True, label="generic-student")
 
 
+# Widths up to 8 run one group of 8 K elements a step.
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("T,V,ds,dt", [(70, 300, 8, 8), (65, 129, 7, 4), (64, 128, 9, 8),
+                                       (130, 1001, 8, 9), (1, 1, 2, 8)])
+def test_generic_kernel_narrow_widths(dtype, T, V, ds, dt):
+    say("generic widths", dtype, T, V, ds, dt)
+    wl = custom("narrow", num_seqs=1, seq_len=T, vocab=V, d_student=ds, d_teacher=dt,
+                dtype=dtype, cut_rule=("frac", 0.0, 0.0), target_source="uniform")
+    hip = run_hip(wl, outputs=FORWARD + ("kl_rev",))
+    assert hip["stats"]["kernel"] == "generic"
+    compare(hip, wl, label="widths-%s-%d-%d" % (dtype, ds, dt))
+    alone = run_hip(wl, outputs=("logp_s", "am_s"), student_only=True)
+    compare(alone, wl, student_only=True, label="widths-student")
+
+
 def test_generic_kernel_nan_and_infinite_rows_stay_their_own():
     say("generic kernel, rows with NaN and infinite hidden states")
     wl = custom("generic-nan", num_seqs=1, seq_len=70, vocab=300, d_student=33, d_teacher=64,
