@@ -49,7 +49,7 @@ def test_few_positions_many_splits(T, outs, narrow):
                   student_only=outs == "student", narrow=narrow)
     ns = hip["stats"]["splits"]
     assert hip["stats"]["kernel"] == "mfma"
-    # (calls of a context on the 256 x 128 kernel take 64 at most, as its top-K lists do)
+    # (calls on the 256 x 128 kernel take 64 at most, as its top-K lists do)
     assert ns >= 64 if T <= 300 else ns <= 32, ns
     assert hip["stats"]["flagged"] >= 1 and hip["am_s"][0] == min(j, V - 1)
     compare(hip, wl, student_only=outs == "student", label="few-%d-%s" % (T, outs))
@@ -120,6 +120,46 @@ def test_backward_product_splits(T, ds, V, layout):
         for k in ("h", "w"):
             np.testing.assert_array_equal(hip[k], again[k], err_msg=k)
     check_grads(hip, oracle_backward(wl, 1.0, 0.0, O.REGION_TEACHER), wl, "product-%d" % T)
+
+
+# dL/dW with more 256 x 256 tiles than compute units (274 x 2): a workgroup's pipeline goes on
+# into its next tile, with one K step a tile (A's prefetch two tiles ahead) and with three,
+# whole tiles and ragged ones, values stored one by one (odd V, [d][V]) and in fours.
+@pytest.mark.parametrize("T,V", [(40, 70001), (40, 70000), (150, 70001)])
+@pytest.mark.parametrize("layout", [L.OLIVE_W_DV, L.OLIVE_W_VD], ids=["dv", "vd"])
+def test_backward_product_units_follow_each_other(T, V, layout):
+    say("backward product, several units a workgroup", T, V, layout)
+    wl = custom("units", num_seqs=1, seq_len=T, vocab=V, d_student=320, d_teacher=64,
+                cut_rule=("frac", 0.0, 0.0), target_source="uniform")
+    hip = run_backward(wl, layout=layout)
+    check_grads(hip, oracle_backward(wl, 1.0, 0.0, O.REGION_TEACHER), wl, "units-%d" % T)
+
+
+# The same onto C: a second chunk of rows (8 past 8192) adds to 36 x 8 tiles, the loads of C
+# behind the next tile's prefetches. Sampled columns and rows against the oracle.
+def test_backward_product_units_add_a_second_chunk():
+    say("backward product, several units a workgroup, second chunk")
+    T, V, ds = 8200, 9001, 2048
+    wl = custom("units2", num_seqs=1, seq_len=T, vocab=V, d_student=ds, d_teacher=64,
+                cut_rule=("frac", 0.0, 0.0), target_source="uniform")
+    rng = np.random.default_rng(5)
+    cols = np.unique(np.concatenate([[0, 255, 256, V - 1], rng.choice(V, 60, replace=False)]))
+    rows = np.unique(np.concatenate([[0, 8191, 8192, T - 1], rng.choice(T, 28, replace=False)]))
+    f64 = lambda t: to_np(t).astype(np.float64)   # noqa: E731
+    hs, ws, y = f64(wl["h_student"]), f64(wl["w_student"]), to_np(wl["targets"])
+    # the logit gradients of every row: p - onehot(y)
+    z = hs @ ws
+    z -= z.max(axis=1, keepdims=True)
+    np.exp(z, out=z)
+    z /= z.sum(axis=1, keepdims=True)
+    z[np.arange(T), y] -= 1.0
+    ref = {"rows": np.arange(T), "in_region": np.ones(T, dtype=bool), "g": z,
+           "grad_w": hs.T @ z[:, cols], "grad_h": np.zeros((T, ds))}
+    ref["grad_h"][rows] = z[rows] @ ws.T
+    for layout in (L.OLIVE_W_DV, L.OLIVE_W_VD):
+        hip = run_backward(wl, layout=layout)
+        check_grads({"w": hip["w"]}, ref, wl, "units2-w-%d" % layout, cols=cols)
+        check_grads({"h": hip["h"]}, ref, wl, "units2-h-%d" % layout, rows=rows)
 
 
 # dL/dW of few tiles (three here) runs on as many compute units as dL/dh: over 9000 rows the
@@ -266,9 +306,10 @@ def test_generic_exact_decision_parts(dtype, ties):
     compare(hip, wl, label="parts-%s-%d" % (dtype, ties))
 
 
-# A call without a context forms its weight norms itself: in the scoring pass (from the
-# units of position tile 0; V = 3001 shifts the last vocabulary tile), or after it for the
-# models with flagged rows (generic kernel). Rows 0 and T - 1 tie exactly.
+# A call without a context forms its weight norms itself: in the scoring pass (in vocabulary
+# tile t from the units of position tile t mod their number; V = 3001 shifts the last tile),
+# or after it for the models with flagged rows (generic kernel). Rows 0 and T - 1 tie exactly,
+# which decides by theta's own slack; the norms decide in the test after the next.
 @pytest.mark.parametrize("simple", [False, True], ids=["mfma", "generic"])
 @pytest.mark.parametrize("T,V,scales", [(1, 256, (1.0, 1.0)), (130, 3001, (1.0, 1.0)),
                                         (300, 40000, (2.0, 0.75))])
