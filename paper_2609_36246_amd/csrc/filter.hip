@@ -121,9 +121,10 @@ filter_kernel(ScoreArgs a, FilterQueue w) {
                 const int v = r0 + 8 * (r >> 2) + 4 * hf + (r & 3);
                 if (v < a.V && acc[cb][r] >= thr) {
                     const int n = atomicAdd(&w.qcnt[m * w.cap + q], 1);
-                    if (n < w.ccap) w.cand[((int64_t)m * w.cap + q) * w.ccap + n] = v;
-                    // the first one too many lists the pair for the exhaustive scan
-                    if (n == w.ccap) w.fb[atomicAdd(w.nfb, 1)] = m * w.cap + q;
+                    if (n < w.ccap)
+                        w.cand[((int64_t)m * w.cap + q) * w.ccap + n] = v;
+                    else if (n == w.ccap)   // one too many: listed for the exhaustive scan
+                        w.fb[atomicAdd(w.nfb, 1)] = m * w.cap + q;
                 }
             }
         }
