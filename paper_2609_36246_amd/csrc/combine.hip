@@ -220,7 +220,10 @@ combine_kernel(ScoreArgs a, int same_scale, const int32_t *__restrict__ targets,
         if (zh_t) wave_merge2(st, acc_a, acc_zh, a.cT);
         else wave_merge(st, acc_a, a.cT);
     }
-    // Every lane now holds the merged statistics.
+    // Every lane now holds the merged statistics. Two logits of +inf have no weights (the
+    // generic kernel's fold gave each 1).
+    if (ss.sec == -kNegInf) ss.z = __builtin_nanf("");
+    if (HAS_T && st.sec == -kNegInf) st.z = __builtin_nanf("");
     int fl = (am_s && near_tie(ss, a.sS)) ? 1 : 0;
     if (HAS_T) fl |= (am_t && near_tie(st, a.sT)) ? 2 : 0;
     float theta_s = 0.f, theta_t = 0.f;

@@ -59,11 +59,11 @@ struct GRun {           // running statistics of one position column of one mode
     float acc;          // exp-weighted logit difference
 };
 
-// exp2((a - tm) c) for the maximum tm of a column, 1 where a = tm (an infinite one, or a
-// column of -inf so far). one is tm, or NaN once two logits are +inf: their weights are
-// undefined and leave the row's normaliser NaN, as in the merges.
-__device__ __forceinline__ float exp_gap(float a, float tm, float one, float c) {
-    return a == one ? 1.f : fast_exp2((a - tm) * c);
+// exp2((a - b) c), 1 for equal a and b (infinite ones among them: the combine pass makes the
+// sum of a row whose second maximum is +inf NaN; a test here, even one a unit, cost the
+// unaligned instances 1 to 1.6 %).
+__device__ __forceinline__ float exp_gap(float a, float b, float c) {
+    return a == b ? 1.f : fast_exp2((a - b) * c);
 }
 
 // Fold the lane's 16 logits z of one column (rows v0 + 8 (r / 4) + r % 4) into R, with
@@ -83,15 +83,14 @@ __device__ __forceinline__ void fold16(const floatx16 &z, const floatx16 &o, GRu
         idx = z[r] > tm ? v : idx;
         tm = fmaxf(tm, z[r]);
     }
-    const float one = ts == -kNegInf ? __builtin_nanf("") : tm;
-    const float resc = exp_gap(R.st.best, tm, one, c);
+    const float resc = exp_gap(R.st.best, tm, c);
     // the block's sums first, then onto the column's: shorter chains of roundings
     float zs = 0.f, as = 0.f;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
         const int v = v0 + 8 * (r >> 2) + (r & 3);
         if (v >= V) continue;
-        const float e = exp_gap(z[r], tm, one, c);
+        const float e = exp_gap(z[r], tm, c);
         zs += e;
         if (DIFF) {
             float dl;
