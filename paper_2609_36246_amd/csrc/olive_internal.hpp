@@ -243,13 +243,14 @@ constexpr uint64_t gemm_split_key(int S, uint32_t n_tiles, int ksteps, int G, in
 // Whether a product of up to `tiles` tiles and `ksteps` K steps may be split at all: where
 // not, the launch that adds the parts (4 us, a K step takes 1.1) is saved. Not for one round
 // of the grid with few K steps (32 rows, V = 300, d_S = 64: dL/dh's 5 steps 9.8 us, in 5
-// parts 12.3 + 3.9), and not for dL/dW (known: its `tiles` are exact) from half the grid on,
-// where its at most 128 steps leave little to gain. With few tiles they ran on as many
-// compute units: 9000 rows, V = 600, d_S = 64, 3 tiles: 195 us of the 345 of a backward,
-// which takes 201.
-constexpr bool gemm_may_split(int64_t tiles, int64_t ksteps, int G, bool known) {
-    if (tiles <= G && ksteps <= 5) return false;
-    return !known || 2 * tiles <= G;
+// parts 12.3 + 3.9), and not for dL/dW (dw: `ksteps` bounds its rows) of few rows (about 330
+// of 700 scored, V = 2633, d_S = 384: 115.5 us without, 119.5 with the launch) or from half the
+// grid on, where its at most 128 steps leave little to gain. With few tiles they ran on as
+// many compute units: 9000 rows, V = 600, d_S = 64, 3 tiles: 195 us of the 345 of a
+// backward, which takes 201.
+constexpr bool gemm_may_split(int64_t tiles, int64_t ksteps, int G, bool dw) {
+    if (dw) return 2 * tiles <= G && ksteps >= 16;
+    return tiles > G || ksteps > 5;
 }
 
 // Partial tiles kept for a product of up to `tiles` tiles and `ksteps` K steps: a second part
