@@ -142,10 +142,12 @@ __device__ __forceinline__ bool near_tie(const Stat &st, float s) {
     return gap <= kTieWindow * (mag > 1.f ? mag : 1.f);
 }
 
-// MANY: more rows than the SIMDs hold at 4 wavefronts each, of widths whose loads fit 64
+// MANY: rows for several rounds of 4 wavefronts a SIMD, of widths whose loads fit 64
 // registers: 8 wavefronts a SIMD hide the latency instead of the loads in flight (108
 // registers). 100000 positions at d = 512 96 against 139 us, 16384 at d 512 + 1024 25 against
-// 29.5; but 160 at d 2048 + 4096 in 198 splits 24.8 against 19.5, 6144 28.6 against 25.6.
+// 29.5, 8192 13.6 against 14.9 (d = 64); but 160 at d 2048 + 4096 in 198 splits 24.8 against
+// 19.5, 6144 28.6 against 25.6. likely_rows: the call's positions, a quarter of them where
+// only the region is compacted.
 template <typename E, bool HAS_T, bool MANY>
 __global__ void __launch_bounds__(256, MANY ? 8 : 1)
 combine_kernel(ScoreArgs a, int same_scale, const int32_t *__restrict__ targets,
@@ -422,11 +424,12 @@ hipError_t launch_combine(const ScoreArgs &a, bool bf16, bool has_t, bool same_s
                           const int32_t *targets, int32_t *err, float *logp_s, float *logp_t,
                           int32_t *am_s, int32_t *am_t, float *kl, float *kl_rev, float *logp_tmp,
                           float *lse_out, int32_t *flagged, int flag_cap,
-                          const FilterQueue &fq, int64_t max_rows, hipStream_t st) {
+                          const FilterQueue &fq, int64_t max_rows, int64_t likely_rows,
+                          hipStream_t st) {
     if (max_rows <= 0) return hipSuccess;
     dim3 grid((unsigned)((max_rows + 3) / 4));
     int same = same_scale ? 1 : 0;
-    const bool many = bf16 && max_rows > 4096 && a.ds <= 2048 && a.dt <= 2048;
+    const bool many = bf16 && likely_rows > 8192 && a.ds <= 2048 && a.dt <= 2048;
 #define OLIVE_COMBINE(E_, T_, M_)                                                             \
     combine_kernel<E_, T_, M_><<<grid, 256, 0, st>>>(a, same, targets, err, logp_s, logp_t,   \
                                                      am_s, am_t, kl, kl_rev, logp_tmp,        \

@@ -295,7 +295,8 @@ olive_status run(olive_score_ctx *ctx, const olive_batch *b, const olive_spans *
     s = check_hip(launch_combine(a, ctx->bf16, has_t, same_scale, b->targets, ctx->err, logp_s,
                                  has_t ? logp_t : nullptr, am_s, has_t ? am_t : nullptr,
                                  has_t ? kl : nullptr, has_t ? kl_rev : nullptr, logp_tmp,
-                                 lse_out, flagged, ctx->flag_cap, fq, T, st));
+                                 lse_out, flagged, ctx->flag_cap, fq, T,
+                                 region_only ? T / 4 : T, st));
     if (s) return s;
     if (mfma && ctx->bw && lse_out) {
         ctx->fwd_lse = lse_out;
@@ -444,7 +445,7 @@ olive_status run_backward(olive_score_ctx *ctx, const olive_batch *b, const oliv
         if (s) return s;
         s = check_hip(launch_combine(a, true, has_t, same_scale, b->targets, ctx->err, nullptr,
                                      nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
-                                     ctx->bw_lse, nullptr, 0, FilterQueue{}, T, st));
+                                     ctx->bw_lse, nullptr, 0, FilterQueue{}, T, T / 4, st));
         if (s) return s;
         lse = ctx->bw_lse;
         if (wide) {

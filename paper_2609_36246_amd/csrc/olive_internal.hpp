@@ -310,7 +310,8 @@ hipError_t launch_combine(const ScoreArgs &a, bool bf16, bool has_t, bool same_s
                           const int32_t *targets, int32_t *err, float *logp_s, float *logp_t,
                           int32_t *am_s, int32_t *am_t, float *kl, float *kl_rev, float *logp_tmp,
                           float *lse_out, int32_t *flagged, int flag_cap,
-                          const FilterQueue &fq, int64_t max_rows, hipStream_t st);
+                          const FilterQueue &fq, int64_t max_rows, int64_t likely_rows,
+                          hipStream_t st);
 hipError_t launch_topk(const ScoreArgs &a, const TopkWork &w, const TopkOut &out,
                        int64_t max_rows, hipStream_t st);
 hipError_t launch_argmax_fix(const ScoreArgs &a, const FilterQueue &q, int32_t *am_s,

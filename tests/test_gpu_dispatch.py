@@ -55,8 +55,8 @@ def test_few_positions_many_splits(T, outs, narrow):
     compare(hip, wl, student_only=outs == "student", label="few-%d-%s" % (T, outs))
 
 
-# The combine pass holds fewer registers from 4097 positions on, up to widths of 2048.
-@pytest.mark.parametrize("T,ds,dt", [(4096, 64, 128), (4097, 64, 128), (4097, 128, 2112)])
+# The combine pass holds fewer registers from 8193 positions on, up to widths of 2048.
+@pytest.mark.parametrize("T,ds,dt", [(8192, 64, 128), (8193, 64, 128), (8193, 128, 2112)])
 @pytest.mark.parametrize("student", [False, True], ids=["both", "student"])
 def test_combine_of_many_positions(T, ds, dt, student):
     say("combine", T, ds, dt, student)
