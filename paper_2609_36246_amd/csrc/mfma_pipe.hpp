@@ -1,6 +1,6 @@
-// Pieces of the bf16 MFMA operand pipeline shared by the scoring kernel and the
-// GEMM kernels: operand types, the 3-stage LDS ring of (256 x 128-byte, 128 x
-// 128-byte) tiles fed by global->LDS DMAs, its swizzle and wait-count encodings.
+// Pieces of the bf16 MFMA operand pipelines: operand types, DMAs, swizzle and wait-count
+// encodings, which the scoring kernels and the products share, and the 256 x 128 scoring
+// kernel's 3-stage LDS ring of (256 x 128-byte, 128 x 128-byte) tiles.
 #pragma once
 
 #include <hip/hip_runtime.h>

@@ -57,7 +57,7 @@ struct olive_score_ctx {
     uint16_t *bw_hrt = nullptr;                 // [d_S][chunk]
     float *bw_mref = nullptr;                   // [vocabulary tiles][chunk], then gy [chunk]
                                                 // and yrow [chunk] (int32)
-    float *bw_gws = nullptr;                    // partial tiles of the dL/dh product
+    float *bw_gws = nullptr;                    // partial tiles of the products
     int64_t bw_gtiles = 0;
     // Normalisers of the last forward call on the MFMA path and the batch they belong
     // to, for a backward on that batch (OLIVE_GRAD_REUSE_FORWARD). Scored rows take the
@@ -223,15 +223,17 @@ olive_status run(olive_score_ctx *ctx, const olive_batch *b, const olive_spans *
     const int grid = mfma ? ctx->n_cu : SIMPLE_WG * ctx->n_cu;
     const int vrows = mfma ? MFMA_BV : SIMPLE_VC;
     const int n_vtiles = (int)((V + vrows - 1) / vrows);
-    s = check_hip(launch_prep(*b, spans, region_only, V, ctx->seqbuf, ctx->sched, ctx->err, counts,
+    s = check_hip(launch_prep(*b, spans, region_only, ctx->seqbuf, ctx->sched, ctx->err, counts,
                               wide ? WIDE_BT : (mfma ? MFMA_BT : SIMPLE_BT), n_vtiles, grid,
-                              // (every call of a context on the 256 x 128 kernel alike:
-                              // asking for top-K leaves the other outputs as they are)
+                              // (every call on the 256 x 128 kernel alike, of contexts
+                              // with and without top-K: asking for it leaves the other
+                              // outputs' bits as they are. Without lists more splits
+                              // than MAX_SPLITS_TOPK would pay for few positions, but
+                              // sum in another order)
                               mfma && !wide && !ctx->no_init ? topk_min_splits(n_vtiles) : 1,
                               ctx->fstride, jsd ? MFMA_BT : 0, kOneChunk, st));
     if (s) return s;
-    s = check_hip(launch_rowmap(*b, spans, region_only, V, ctx->seqbuf, ctx->sched, ctx->rowmap,
-                                ctx->err,
+    s = check_hip(launch_rowmap(*b, spans, region_only, ctx->seqbuf, ctx->sched, ctx->rowmap,
                                 logp_s,
                                 has_t ? logp_t : nullptr, am_s, has_t ? am_t : nullptr,
                                 has_t ? kl : nullptr, has_t ? kl_rev : nullptr,
@@ -386,14 +388,14 @@ olive_status run_backward(olive_score_ctx *ctx, const olive_batch *b, const oliv
     // pass runs the 256 x 256 kernel where the context keeps its panels, the gradient
     // passes take 128-row tiles.
     auto schedule = [&](int tile_rows) {
-        olive_status e = check_hip(launch_prep(*b, spans, true, V, ctx->seqbuf, ctx->sched,
+        olive_status e = check_hip(launch_prep(*b, spans, true, ctx->seqbuf, ctx->sched,
                                                ctx->err, go->counts, tile_rows, n_vtiles,
                                                grid, 1, ctx->fstride,
                                                wide_dz ? WIDE_BT : MFMA_BT, ch, st));
         if (!e)
-            e = check_hip(launch_rowmap(*b, spans, true, V, ctx->seqbuf, ctx->sched, ctx->rowmap,
-                                        ctx->err, nullptr, nullptr, nullptr, nullptr, nullptr,
-                                        nullptr, nullptr, nullptr, TopkOut{}, st));
+            e = check_hip(launch_rowmap(*b, spans, true, ctx->seqbuf, ctx->sched, ctx->rowmap,
+                                        nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
+                                        nullptr, nullptr, TopkOut{}, st));
         return e;
     };
     olive_status s = schedule(wide && !online ? WIDE_BT : MFMA_BT);

@@ -269,14 +269,14 @@ hipError_t launch_filter(const ScoreArgs &a, const FilterQueue &q, hipStream_t s
 hipError_t launch_repack(const void *w_dv, void *w_vd, int64_t d, int64_t V, int elem_bytes,
                          hipStream_t st);
 hipError_t launch_prep(const olive_batch &b, const olive_spans *spans, bool region_only,
-                       int64_t V, int32_t *seqbuf, Sched *sched, int32_t *err, int64_t *counts,
-                       int tile_rows, int n_vtiles, int grid, int min_splits, int64_t fstride, int pass_tile, int pass_chunk,
-                       hipStream_t st);
+                       int32_t *seqbuf, Sched *sched, int32_t *err, int64_t *counts,
+                       int tile_rows, int n_vtiles, int grid, int min_splits, int64_t fstride,
+                       int pass_tile, int pass_chunk, hipStream_t st);
 hipError_t launch_rowmap(const olive_batch &b, const olive_spans *spans, bool region_only,
-                         int64_t V, const int32_t *seqbuf,
-                         const Sched *sched, uint32_t *rowmap, int32_t *err, float *logp_s,
-                         float *logp_t, int32_t *am_s, int32_t *am_t, float *kl, float *kl_rev,
-                         float *jsd, float *logp_tmp, const TopkOut &tk, hipStream_t st);
+                         const int32_t *seqbuf, const Sched *sched, uint32_t *rowmap,
+                         float *logp_s, float *logp_t, int32_t *am_s, int32_t *am_t,
+                         float *kl, float *kl_rev, float *jsd, float *logp_tmp,
+                         const TopkOut &tk, hipStream_t st);
 hipError_t launch_score_simple(const ScoreArgs &a, bool bf16, bool has_t, int grid,
                                hipStream_t st);
 hipError_t launch_score_mfma(const ScoreArgs &a, bool has_t, bool same_scale, bool rev,

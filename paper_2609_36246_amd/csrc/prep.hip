@@ -406,10 +406,9 @@ static SpanArgs span_args(const olive_spans *s) {
 }
 
 hipError_t launch_prep(const olive_batch &b, const olive_spans *spans, bool region_only,
-                       int64_t V, int32_t *seqbuf, Sched *sched, int32_t *err, int64_t *counts,
-                       int tile_rows, int n_vtiles, int grid, int min_splits, int64_t fstride, int pass_tile, int pass_chunk,
-                       hipStream_t st) {
-    (void)V;
+                       int32_t *seqbuf, Sched *sched, int32_t *err, int64_t *counts,
+                       int tile_rows, int n_vtiles, int grid, int min_splits, int64_t fstride,
+                       int pass_tile, int pass_chunk, hipStream_t st) {
     prep_kernel<<<1, PREP_THREADS, 0, st>>>(b.cu_seqlens, b.cut, b.valid_len, b.num_seqs,
                                             b.total_positions, b.region, span_args(spans),
                                             region_only ? 1 : 0, seqbuf, sched, err, counts,
@@ -420,11 +419,9 @@ hipError_t launch_prep(const olive_batch &b, const olive_spans *spans, bool regi
 }
 
 hipError_t launch_rowmap(const olive_batch &b, const olive_spans *spans, bool region_only,
-                         int64_t V, const int32_t *seqbuf,
-                         const Sched *sched, uint32_t *rowmap, int32_t *err, float *logp_s,
-                         float *logp_t, int32_t *am_s, int32_t *am_t, float *kl, float *kl_rev,
+                         const int32_t *seqbuf, const Sched *sched, uint32_t *rowmap,
+                         float *logp_s, float *logp_t, int32_t *am_s, int32_t *am_t, float *kl, float *kl_rev,
                          float *jsd, float *logp_tmp, const TopkOut &tk, hipStream_t st) {
-    (void)V; (void)err;
     int64_t T = b.total_positions;
     int64_t blocks = (T + 255) / 256;
     if (blocks > 4096) blocks = 4096;

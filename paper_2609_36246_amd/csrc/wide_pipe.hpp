@@ -1,5 +1,5 @@
-// The operand pipeline of the 256 x 256 MFMA kernels for gfx950 (the scoring kernel and
-// its logit-gradient pass, the backward's dL/dh product): 4 wavefronts own a 256 x 256
+// The operand pipeline of the 256 x 256 scoring kernels for gfx950 (the scoring pass and the
+// logit-gradient passes of the cross-entropy): 4 wavefronts own a 256 x 256
 // fp32 tile, wavefront w all 256 A rows of B rows 64w .. 64w+63, as 16 x 4 blocks of
 // v_mfma_f32_16x16x32_bf16 in 256 AGPRs. K advances 32 elements per step. A step's A tile
 // (256 rows x 64 bytes) and B tile (256 rows x 64 bytes) land in one of 3 LDS stages
