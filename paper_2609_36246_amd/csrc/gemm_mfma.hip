@@ -477,7 +477,7 @@ hipError_t launch_gemm(const GemmArgs &g, int grid, hipStream_t st) {
     }
     if (g.ws) {
         const int64_t rows = tiles_of(g.M, GT) * tiles_of(g.n_dev ? g.n_cap : g.N, GT) * GT;
-        const int64_t blocks = (rows + 3) / 4 < 2 * grid ? (rows + 3) / 4 : 2 * grid;
+        const int64_t blocks = (rows + 3) / 4 < 4 * grid ? (rows + 3) / 4 : 4 * grid;
         gemm_reduce_kernel<<<(unsigned)blocks, 256, 0, st>>>(g, grid);
     }
     return hipGetLastError();
