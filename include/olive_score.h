@@ -101,7 +101,8 @@ typedef struct {
 /* Reserve the workspace of the top-K statistics (olive_score_outputs' topk_* and
  * kl_topk fields). Needs a bf16 teacher context on which the MFMA kernel applies and
  * 512 <= V <= 2^23 (else init returns E_UNSUPPORTED). The workspace holds about
- * max_positions x 6.7 KB of device memory. */
+ * max_positions x 6.7 KB of device memory, and 9 MB at least on 256 compute units with
+ * V >= 32768 (calls of few positions take more vocabulary splits). */
 #define OLIVE_FLAG_TOPK 4
 /* Reserve the workspace of olive_score_backward. Needs a bf16 context on which the
  * MFMA kernel applies (else init returns E_UNSUPPORTED). The workspace holds about
